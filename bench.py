@@ -419,7 +419,7 @@ def main():
         traffic = measured_traffic(wdf, ens, args.workload, gather) if gather else None
         roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK_OPS / 1e12, "unit": "Tops/s",
                     "frac": achieved / VALU_PEAK_OPS, "traffic": traffic,
-                    "kernel": f"wdf_explain_{gather}" if gather else "k_explain_generic", "kernel_ms": explain_ms,
+                    "kernel": f"wdf_explain_{gather}" if gather else "k_walk", "kernel_ms": explain_ms,
                     "ops_per_row": ops_row}
     base = bg.base_value
     rows_check = np.sort(np.random.default_rng(2511).choice(n, min(n, args.cpu_rows), replace=False))

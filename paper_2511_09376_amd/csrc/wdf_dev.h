@@ -95,4 +95,50 @@ constexpr int64_t ivunit_floats(const IvUnit &u) {
   return (((int64_t)(4 * ivunit_quads(u.cnt) + ivunit_tail(u.cnt)) << u.depth) + 3) & ~(int64_t)3;
 }
 
+// The data-driven kernels (k_walk, k_hist_walk) run walk programs: one op per
+// tested node of a tree, depth first, on a wave of 64 rows (one per lane).  A
+// lane keeps the raw splits of its current path in one register P (root in
+// the top bit, bit 1: the row went left); an op drops the levels the walk went
+// back up, shifts its split in and, at the last node of a unit, hands out the
+// unit's index I = P as slot I ^ (I >> fold_a) ^ (I >> fold_b) ^ mask.
+struct WalkOp {
+  int32_t feat;
+  uint32_t key;   // walk_key(threshold) - bias: the row goes left iff walk_key(x) - bias < key (unsigned)
+  uint32_t ctl;   // bits 0-3 levels to drop, bit 4 bias (1: a NaN goes right), bit 5 emit, 8-12 fold_a, 16-20 fold_b (31: no term)
+  uint32_t out;   // bits 0-19 where the slot goes (a pattern row of the chunk, or its first bin), 20-31 mask
+};
+constexpr uint32_t kWalkBias = 1u << 4, kWalkEmit = 1u << 5;
+
+// Totally ordered image of a float: x < y iff walk_key(x) < walk_key(y), both
+// zeros alike, every NaN 0 (below all numbers; a bias of 1 wraps it above them).
+constexpr uint32_t walk_key_bits(uint32_t b) {
+  return (b & 0x7fffffffu) > 0x7f800000u ? 0u : b == 0x80000000u ? 0x80000000u : (b >> 31) ? ~b : b | 0x80000000u;
+}
+
+// One group of output columns: the column range and its chunks of units.
+struct WalkGroup {
+  int64_t col0;
+  int32_t chunk0, chunk1;
+};
+// Units whose patterns a block holds in LDS together: the tree segments that
+// compute them (op ranges) and the column runs that read them.
+struct WalkChunk {
+  int32_t seg0, seg1, run0, run1;
+};
+// Zeros for columns [zero0, col), then the sum of entries [e0, e1) for column
+// col (none when empty); columns are relative to the group's.
+struct WalkRun {
+  int32_t zero0, col, e0, e1;
+};
+// One table value: pattern row slot4 >> 2 of the chunk, tables at float
+// 4 tab16 + (slot4 & 3).
+struct WalkEntry {
+  uint32_t slot4, tab16;
+};
+// A chunk of the data-driven histogram: groups whose bins fit the LDS.
+struct WalkHistChunk {
+  int64_t bin0;
+  int32_t bins, seg0, seg1, pad;
+};
+
 }  // namespace wdf

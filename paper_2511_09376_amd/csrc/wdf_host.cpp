@@ -115,6 +115,7 @@ extern "C" int wdf_create(int device, wdf_ctx **out) {
   // the device address of the scratch array of the no-alloc entry points,
   // resolved once per context with its device current
   HIP_TRY(scratch_address(&c->scratch));
+  HIP_TRY(walk_init());
   HIP_TRY(hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking));
   *out = c.release();
   return WDF_OK;
@@ -461,12 +462,20 @@ extern "C" int wdf_model_load(wdf_ctx *ctx, const wdf_model_desc *desc, int kern
     return set_error(WDF_E_OOM, "wdf_model_load: out of host memory");
   }
   if ((rc = upload_model(M.get()))) return rc;
+  M->jp.quad_depth = quads ? WDF_MAX_DEPTH : 0;
   if (kernel != WDF_KERNEL_GENERIC) {
-    M->jp.quad_depth = quads ? WDF_MAX_DEPTH : 0;
     rc = jit_build(M.get());
     if (rc != WDF_OK) {
       if (kernel == WDF_KERNEL_SPECIALISED) return rc;
       M->jit.reset();  // AUTO: keep the generic kernels
+    }
+  }
+  if (!M->jit) {
+    try {
+      plan_units(M.get(), INT64_MAX);
+      if ((rc = walk_build_explain(M.get())) || (rc = walk_build_hist(M.get()))) return rc;
+    } catch (const std::bad_alloc &) {
+      return set_error(WDF_E_OOM, "wdf_model_load: out of host memory");
     }
   }
   *out = M.release();
@@ -651,7 +660,7 @@ static int alloc_tables(wdf_model *M, wdf_bg *bg, hipStream_t s) {
   const int64_t n = bg->iv ? M->iv_tab_size + 256 : M->tab_size;
   if ((rc = bg->d_tab.alloc((size_t)std::max<int64_t>(n, 1) * sizeof(float)))) return rc;
   HIP_TRY(hipMemsetAsync(bg->d_tab.ptr, 0, bg->d_tab.bytes, s));
-  if (M->jit && !bg->iv) {
+  if (!bg->iv) {
     if ((rc = bg->d_xtab.alloc((size_t)std::max<int64_t>(M->jp.xtab_size, 1) * sizeof(float)))) return rc;
     HIP_TRY(hipMemsetAsync(bg->d_xtab.ptr, 0, bg->d_xtab.bytes, s));
   }
@@ -709,9 +718,8 @@ static int enqueue_contract(wdf_model *M, wdf_bg *bg, const uint32_t *hist, cons
   if ((rc = enqueue_gemms(M, bg, H, S, s, nullptr))) return rc;
   HIP_TRY(launch_expand(M->d_groups.as<Group>(), M->d_path.as<PathNode>(), G, M->d_sclass_off.as<int64_t>(), S,
                         bg->d_tab.as<float>(), nullptr, s));
-  if (M->jit)  // explain tables of the specialised kernel
-    HIP_TRY(launch_xtab(M->jp.d_xunits.as<XUnit>(), (int64_t)M->jp.xunits.size(), bg->d_tab.as<float>(),
-                        bg->d_xtab.as<float>(), s));
+  HIP_TRY(launch_xtab(M->jp.d_xunits.as<XUnit>(), (int64_t)M->jp.xunits.size(), bg->d_tab.as<float>(),
+                      bg->d_xtab.as<float>(), s));
   HIP_TRY(launch_base(M->d_groups.as<Group>(), G, hist, freq, freq_r, hist ? 1.0 / (double)bg->m : 1.0, base, s));
   return WDF_OK;
 }
@@ -777,8 +785,7 @@ extern "C" int wdf_background_load(wdf_model *M, const float *B, int64_t m, int6
     if ((rc = ws_reserve(M->ws_codes, (size_t)M->jp.words * (size_t)m * sizeof(uint32_t)))) return rc;
     if ((rc = jit_hist(M, Bd, m, ldb, bg->d_hist.as<uint32_t>(), M->ws_codes.as<uint32_t>(), s))) return rc;
   } else {
-    HIP_TRY(launch_hist_generic(M->d_groups.as<Group>(), M->d_path.as<PathNode>(), (int64_t)M->groups.size(), Bd,
-                                m, ldb, bg->d_hist.as<uint32_t>(), s));
+    if ((rc = walk_hist(M, Bd, m, ldb, bg->d_hist.as<uint32_t>(), s))) return rc;
   }
   if ((rc = contract(M, bg.get(), bg->d_hist.as<uint32_t>(), nullptr, 1.0 / (double)m, s))) return rc;
   ++M->n_bg;
@@ -816,8 +823,7 @@ static int enqueue_refresh(wdf_bg *bg, const float *B, int64_t ldb, hipStream_t 
   if (M->jit) {
     if ((rc = jit_hist(M, B, m, ldb, bg->d_hist.as<uint32_t>(), bg->own_codes.as<uint32_t>(), s))) return rc;
   } else {
-    HIP_TRY(launch_hist_generic(M->d_groups.as<Group>(), M->d_path.as<PathNode>(), (int64_t)M->groups.size(), B, m,
-                                ldb, bg->d_hist.as<uint32_t>(), s));
+    if ((rc = walk_hist(M, B, m, ldb, bg->d_hist.as<uint32_t>(), s))) return rc;
   }
   return enqueue_contract(M, bg, bg->d_hist.as<uint32_t>(), nullptr, 1.0 / (double)m, bg->own_H.as<double>(),
                           bg->own_S.as<double>(), bg->d_base.as<double>(), s);
@@ -967,10 +973,8 @@ extern "C" int wdf_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t 
   if (bg->iv) return set_error(WDF_E_INVALID_ARG, "wdf_explain: an interaction summary: use wdf_explain_iv");
   wdf_model *M = bg->model;
   hipStream_t s = pick_stream(M->ctx, hip_stream);
-  if (M->jit) return jit_explain(bg, X, n, ldx, phi, ldphi, s);
-  HIP_TRY(launch_explain_generic(M->d_groups.as<Group>(), M->d_path.as<PathNode>(), (int64_t)M->groups.size(),
-                                 bg->d_tab.as<float>(), X, n, ldx, phi, ldphi, M->n_features, s));
-  return WDF_OK;
+  if (M->jit && n > kWalkMaxRows) return jit_explain(bg, X, n, ldx, phi, ldphi, s);
+  return walk_explain(bg, X, n, ldx, phi, ldphi, s);
 }
 
 extern "C" int64_t wdf_explain_iv_workspace(const wdf_bg *bg, int64_t n) {

@@ -83,6 +83,28 @@ struct ClassInfo {
   int64_t s_off = 0;      // offset (doubles) of this class in the product buffer
 };
 
+// Plan of the data-driven gather (wdf_walk.cpp): one level, i.e. one choice of
+// output columns per block.
+struct WalkLevel {
+  int n_groups = 0, max_slots = 1, entry_shift = 4;
+  bool wide = false;
+  int64_t n_entries = 0;
+  DevBuf ops, segs, groups, chunks, runs, entries;
+};
+// Plan of the data-driven histogram.
+struct WalkHist {
+  int n_chunks = 0, n_roots = 0;
+  DevBuf ops, segs, chunks, roots;
+};
+// Rows up to which a specialised model explains through the data-driven gather
+// (100 depth-6 trees, us): 1 row 20 against 135 of the generated kernel, 1000
+// rows 66 / 137, 2000 rows 121 / 134, 4096 rows 151 / 132; 100 uneven trees
+// 36 / 178, 66 / 178, 114 / 175, 164 / 173.  The generated kernel streams all
+// tables through the LDS of every CU it uses, a fixed time; the gather's time
+// grows with the rows once its blocks fill the device.
+constexpr int64_t kWalkMaxRows = 2048;
+constexpr int kWalkPatternBytes = 32768;  // pattern rows of a chunk in LDS
+
 }  // namespace wdf
 
 struct wdf_ctx {
@@ -123,6 +145,11 @@ struct wdf_model {
   // model-specialised kernels
   std::shared_ptr<wdf::JitModule> jit;
   wdf::JitPlan jp;
+
+  // data-driven kernels: the explain walk's levels, coarse to fine (rebuilt
+  // with the explain-table units), and the generic models' histogram
+  std::vector<std::unique_ptr<wdf::WalkLevel>> walk;
+  wdf::WalkHist walk_hist;
 
   // workspace of background summaries (threshold codes, contraction columns
   // and products), grown on demand and reused; ws_mu serialises summaries of
@@ -210,4 +237,12 @@ HistLaunch hist_launch(const wdf_model *M, int64_t m);
 // Grow a workspace buffer to at least `bytes` (contents are not kept).
 int ws_reserve(DevBuf &buf, size_t bytes);
 int jit_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, hipStream_t s);
+// the explain-table units of the model, none larger than max_floats as a quad (wdf_jit.cpp)
+void plan_units(wdf_model *M, int64_t max_floats);
+// Data-driven kernels (wdf_walk.cpp): the plan of the explain walk for the
+// planned units (which it uploads), and of the histogram
+int walk_build_explain(wdf_model *M);
+int walk_build_hist(wdf_model *M);
+int walk_hist(const wdf_model *M, const float *B, int64_t m, int64_t ldb, uint32_t *hist, hipStream_t s);
+int walk_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, hipStream_t s);
 }  // namespace wdf

@@ -7,11 +7,41 @@
 
 namespace wdf {
 
-hipError_t launch_hist_generic(const Group *groups, const PathNode *path, int64_t n_groups, const float *B,
-                               int64_t m, int64_t ldb, uint32_t *hist, hipStream_t s);
-hipError_t launch_explain_generic(const Group *groups, const PathNode *path, int64_t n_groups, const float *tab,
-                                  const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, int F,
-                                  hipStream_t s);
+// The data-driven histogram: hist += counts of the rows of B, chunk by chunk
+// of groups; root_bins: the one bin of every tree that is a single leaf.
+struct HistWalkArgs {
+  const float *X;
+  int64_t ldx, m;
+  uint32_t *hist;
+  const WalkOp *ops;
+  const int2 *segs;
+  const WalkHistChunk *chunks;
+  const int64_t *root_bins;
+  int n_chunks, n_root_bins, F, n_cu;
+};
+constexpr int kHistWalkBins = 12288;  // bins of a chunk in LDS (48 KB: with the row keys two blocks fit a CU)
+hipError_t launch_hist_walk(const HistWalkArgs &a, hipStream_t s);
+// The data-driven gather: column c of out (out[c * ldo + row]) is the sum of
+// its table entries.
+struct WalkArgs {
+  const float *X;
+  int64_t ldx, n;
+  float *out;
+  int64_t ldo;
+  const float *tab;
+  const WalkOp *ops;
+  const int2 *segs;
+  const WalkGroup *groups;
+  const WalkChunk *chunks;
+  const WalkRun *runs;
+  const WalkEntry *entries;
+  int F, x_off;  // x_off: byte offset of the row keys in LDS (-1: keys read from X)
+};
+// wide: pattern rows of 16-bit slots (else 8-bit); entry_shift: log2 of the
+// bytes between consecutive slots of a table plane
+// LDS sizes of the data-driven kernels on the current device (once per context)
+hipError_t walk_init();
+hipError_t launch_walk(WalkArgs a, int n_groups, int max_slots, bool wide, int entry_shift, int rows, hipStream_t s);
 hipError_t launch_patterns(const Group *groups, const PathNode *path, int64_t n_groups, const float *X,
                            int64_t n, int64_t ldx, uint32_t *out, hipStream_t s);
 hipError_t launch_columns(const Group *groups, const PathNode *path, int64_t n_groups, const uint32_t *hist,

@@ -113,6 +113,64 @@ void choose_fold(const wdf_model *M, XUnit &u, int64_t tree, const std::vector<i
     }
 }
 
+}  // namespace
+
+void plan_units(wdf_model *M, int64_t max_floats) {
+  JitPlan &P = M->jp;
+  const int64_t G = (int64_t)M->groups.size();
+  // explain-table units: a pair group and the next pair group form a quad
+  // when their pair nodes are the left and right children of one node
+  P.xunits.clear();
+  P.unit_g0.clear();
+  int64_t xoff = 0;
+  for (int64_t g = 0; g < G;) {
+    const Group &ga = M->groups[(size_t)g];
+    bool quad = false;
+    if (ga.depth <= P.quad_depth && g + 1 < G && ga.depth >= 2 && ga.col_r >= 0) {
+      const Group &gb = M->groups[(size_t)g + 1];
+      if (gb.depth == ga.depth && gb.col_r >= 0 && gb.tree == ga.tree) {
+        const size_t la = (size_t)ga.path_off + (size_t)ga.depth, lb = (size_t)gb.path_off + (size_t)gb.depth;
+        quad = M->path_nodes[la - 2] == M->path_nodes[lb - 2] && M->path[la - 2].dir == 0 && M->path[lb - 2].dir == 1;
+      }
+    }
+    XUnit u{};
+    u.src_l = ga.tab_off;
+    u.src_r = quad ? M->groups[(size_t)g + 1].tab_off : -1;
+    u.dst = xoff;
+    u.depth = ga.depth;
+    u.quad = quad ? 1 : 0;
+    u.nv = ga.depth + u.quad;
+    if (quad && xunit_floats(u) > max_floats) {
+      quad = false;
+      u.src_r = -1;
+      u.quad = 0;
+      u.nv = ga.depth;
+    }
+    u.mask = 0;
+    for (int k = 0; k < (quad ? ga.depth - 2 : ga.depth); ++k)
+      u.mask = (u.mask << 1) | M->path[(size_t)ga.path_off + (size_t)k].dir;
+    {
+      // the nodes of the index bits: the group's path (and for a quad the
+      // right pair's node last)
+      std::vector<int64_t> nodes;
+      for (int k = 0; k < ga.depth; ++k) nodes.push_back(M->path_nodes[(size_t)ga.path_off + (size_t)k]);
+      if (quad) {
+        const Group &gb = M->groups[(size_t)g + 1];
+        nodes.push_back(M->path_nodes[(size_t)gb.path_off + (size_t)gb.depth - 1]);
+      }
+      choose_fold(M, u, ga.tree, nodes);
+    }
+    xoff += xunit_floats(u);
+    P.xunits.push_back(u);
+    P.unit_g0.push_back(g);
+    g += quad ? 2 : 1;
+  }
+  P.unit_g0.push_back(G);
+  P.xtab_size = xoff;
+}
+
+namespace {
+
 int make_plan(wdf_model *M) {
   JitPlan &P = M->jp;
   const int F = M->n_features;
@@ -242,55 +300,7 @@ int make_plan(wdf_model *M) {
   if (P.stage_floats < max_table)
     return set_error(WDF_E_UNSUPPORTED, "specialised kernels: %zu thresholds leave too little LDS for the tables",
                      P.thr_pad.size());
-  // explain-table units: a pair group and the next pair group form a quad
-  // when their pair nodes are the left and right children of one node
-  P.xunits.clear();
-  P.unit_g0.clear();
-  int64_t xoff = 0;
-  for (int64_t g = 0; g < G;) {
-    const Group &ga = M->groups[(size_t)g];
-    bool quad = false;
-    if (ga.depth <= P.quad_depth && g + 1 < G && ga.depth >= 2 && ga.col_r >= 0) {
-      const Group &gb = M->groups[(size_t)g + 1];
-      if (gb.depth == ga.depth && gb.col_r >= 0 && gb.tree == ga.tree) {
-        const size_t la = (size_t)ga.path_off + (size_t)ga.depth, lb = (size_t)gb.path_off + (size_t)gb.depth;
-        quad = M->path_nodes[la - 2] == M->path_nodes[lb - 2] && M->path[la - 2].dir == 0 && M->path[lb - 2].dir == 1;
-      }
-    }
-    XUnit u{};
-    u.src_l = ga.tab_off;
-    u.src_r = quad ? M->groups[(size_t)g + 1].tab_off : -1;
-    u.dst = xoff;
-    u.depth = ga.depth;
-    u.quad = quad ? 1 : 0;
-    u.nv = ga.depth + u.quad;
-    if (quad && xunit_floats(u) > P.stage_floats) {
-      quad = false;
-      u.src_r = -1;
-      u.quad = 0;
-      u.nv = ga.depth;
-    }
-    u.mask = 0;
-    for (int k = 0; k < (quad ? ga.depth - 2 : ga.depth); ++k)
-      u.mask = (u.mask << 1) | M->path[(size_t)ga.path_off + (size_t)k].dir;
-    {
-      // the nodes of the index bits: the group's path (and for a quad the
-      // right pair's node last)
-      std::vector<int64_t> nodes;
-      for (int k = 0; k < ga.depth; ++k) nodes.push_back(M->path_nodes[(size_t)ga.path_off + (size_t)k]);
-      if (quad) {
-        const Group &gb = M->groups[(size_t)g + 1];
-        nodes.push_back(M->path_nodes[(size_t)gb.path_off + (size_t)gb.depth - 1]);
-      }
-      choose_fold(M, u, ga.tree, nodes);
-    }
-    xoff += xunit_floats(u);
-    P.xunits.push_back(u);
-    P.unit_g0.push_back(g);
-    g += quad ? 2 : 1;
-  }
-  P.unit_g0.push_back(G);
-  P.xtab_size = xoff;
+  plan_units(M, P.stage_floats);
   // explain stages: consecutive units whose tables fit one LDS buffer (stored
   // as group ranges; a stage never splits a quad)
   P.explain_stages.clear();
@@ -1134,15 +1144,12 @@ int jit_build(wdf_model *M) {
   if (!P.thr_pad.empty() && (e = hipMemcpyAsync(P.d_thr_pad.ptr, P.thr_pad.data(), P.thr_pad.size() * sizeof(float),
                                                 hipMemcpyHostToDevice, s)) != hipSuccess)
     return hip_error(e, "hipMemcpyAsync(padded thresholds)");
-  if ((rc = P.d_xunits.alloc(std::max<size_t>(P.xunits.size(), 1) * sizeof(XUnit)))) return rc;
-  if (!P.xunits.empty() && (e = hipMemcpyAsync(P.d_xunits.ptr, P.xunits.data(), P.xunits.size() * sizeof(XUnit),
-                                               hipMemcpyHostToDevice, s)) != hipSuccess)
-    return hip_error(e, "hipMemcpyAsync(units)");
   if ((rc = P.d_perm.alloc(std::max<size_t>(P.perm.size(), 1) * sizeof(uint32_t)))) return rc;
   if (!P.perm.empty() && (e = hipMemcpyAsync(P.d_perm.ptr, P.perm.data(), P.perm.size() * sizeof(uint32_t),
                                              hipMemcpyHostToDevice, s)) != hipSuccess)
     return hip_error(e, "hipMemcpyAsync(perm)");
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_error(e, "hipStreamSynchronize");
+  if ((rc = walk_build_explain(M))) return rc;
   M->jit = mod;
   return WDF_OK;
 }

@@ -34,41 +34,154 @@ __device__ __forceinline__ uint32_t group_pattern(const Group &g, const PathNode
 // Generic path
 // ---------------------------------------------------------------------------
 
-constexpr int kGroupsPerBlock = 64;
+// The data-driven path: walk programs (WalkOp) instead of generated code.  It
+// serves the models that run no generated kernels, and specialised models where
+// few rows leave the generated explain kernel's one block per 512 rows on a few
+// CUs.
 
-__global__ __launch_bounds__(256) void k_hist_generic(const Group *__restrict__ groups,
-                                                      const PathNode *__restrict__ path, int64_t n_groups,
-                                                      const float *__restrict__ B, int64_t m, int64_t ldb,
-                                                      uint32_t *__restrict__ hist) {
-  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (r >= m) return;
-  const int64_t g0 = (int64_t)blockIdx.y * kGroupsPerBlock;
-  const int64_t g1 = g0 + kGroupsPerBlock < n_groups ? g0 + kGroupsPerBlock : n_groups;
-  for (int64_t gi = g0; gi < g1; ++gi) {
-    const Group g = groups[gi];
-    const uint32_t p = group_pattern(g, path, B, ldb, r);
-    atomicAdd(&hist[g.hist_off + p], 1u);
+constexpr int kWalkThreads = 512, kWalkWaves = kWalkThreads / 64;
+constexpr int kWalkBatch = 16;      // table entries in flight per lane
+constexpr int kWalkXFeatures = 160;  // row keys staged in LDS up to this many features (40 KB)
+
+__device__ __forceinline__ uint32_t walk_key(float x) { return walk_key_bits(__float_as_uint(x)); }
+
+// The row keys of a tile of R rows into LDS: xt[f * R + r].
+template <int R>
+__device__ __forceinline__ void walk_load_tile(const float *__restrict__ X, int64_t ldx, int64_t row0, int64_t n, int F,
+                                               uint32_t *xt) {
+  constexpr int U = 8;
+  for (int i0 = threadIdx.x; i0 < F * R; i0 += kWalkThreads * U) {
+    float x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + kWalkThreads * u, F * R - 1);
+      const int64_t row = row0 + i % R;
+      x[u] = X[(int64_t)(i / R) * ldx + (row < n ? row : n - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + kWalkThreads * u < F * R) xt[i0 + kWalkThreads * u] = walk_key(x[u]);
   }
 }
 
-__global__ __launch_bounds__(256) void k_explain_generic(const Group *__restrict__ groups,
-                                                         const PathNode *__restrict__ path, int64_t n_groups,
-                                                         const float *__restrict__ tab,
-                                                         const float *__restrict__ X, int64_t n, int64_t ldx,
-                                                         float *__restrict__ phi, int64_t ldphi, int F) {
-  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (r >= n) return;
-  for (int f = 0; f < F; ++f) phi[(int64_t)f * ldphi + r] = 0.f;
-  for (int64_t gi = 0; gi < n_groups; ++gi) {
-    const Group g = groups[gi];
-    if (g.depth == 0) continue;
-    const uint32_t p = group_pattern(g, path, X, ldx, r);
-    const float *t = tab + g.tab_off + p;
-    for (int k = 0; k < g.depth; ++k) {
-      const PathNode nd = path[g.path_off + k];
-      if (!nd.first) continue;
-      float *dst = phi + (int64_t)nd.feat * ldphi + r;
-      *dst += t[(int64_t)k << g.depth];
+// One segment (a tree's ops, a multiple of four, at least four): emit(slot,
+// out) at the last node of every unit.  xt: the row's keys, R apart (null: read from X).
+template <int R, class Emit>
+__device__ __forceinline__ void walk_segment(const WalkOp *__restrict__ ops, int2 sg, const float *__restrict__ X,
+                                             int64_t ldx, int64_t row, const uint32_t *xt, Emit emit) {
+  uint32_t P = 0;
+  WalkOp next[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) next[u] = ops[sg.x + u];
+  for (int k = sg.x; k < sg.y; k += 4) {
+    WalkOp o[4];
+    uint32_t x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = next[u];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = xt ? xt[o[u].feat * R] : walk_key(X[(int64_t)o[u].feat * ldx + row]);
+    const int kn = k + 4 < sg.y ? k + 4 : k;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) next[u] = ops[kn + u];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t ctl = o[u].ctl;
+      P = ((P >> (ctl & 15u)) << 1) | (x[u] - ((ctl >> 4) & 1u) < o[u].key ? 1u : 0u);
+      if (ctl & kWalkEmit)
+        emit(P ^ (P >> ((ctl >> 8) & 31u)) ^ (P >> ((ctl >> 16) & 31u)) ^ (o[u].out >> 20), o[u].out & 0xfffffu);
+    }
+  }
+}
+
+// Histograms: a block counts its share of the row tiles for one chunk of
+// groups, whose bins it holds in LDS (the waves take the chunk's trees in
+// turn), and adds the non-zero bins to hist at the end.  Integer counts:
+// exact in any order.
+
+__global__ __launch_bounds__(kWalkThreads) void k_hist_walk(const HistWalkArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t wsmem[];
+  uint32_t *bins = wsmem;
+  uint32_t *xt = a.F <= kWalkXFeatures ? wsmem + kHistWalkBins : nullptr;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const WalkHistChunk ch = a.chunks[blockIdx.y];
+  for (int i = threadIdx.x; i < ch.bins; i += kWalkThreads) bins[i] = 0u;
+  if (blockIdx.x == 0 && blockIdx.y == 0)
+    for (int i = threadIdx.x; i < a.n_root_bins; i += kWalkThreads) atomicAdd(&a.hist[a.root_bins[i]], (uint32_t)a.m);
+  const int64_t tiles = (a.m + 63) / 64;
+  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const int64_t row = t * 64 + lane, rr = row < a.m ? row : a.m - 1;
+    __syncthreads();  // the bins are cleared; the last tile's keys are read
+    if (xt) walk_load_tile<64>(a.X, a.ldx, t * 64, a.m, a.F, xt);
+    __syncthreads();
+    const bool live = row < a.m;
+    for (int s = ch.seg0 + wave; s < ch.seg1; s += kWalkWaves)
+      walk_segment<64>(a.ops, a.segs[s], a.X, a.ldx, rr, xt ? xt + lane : nullptr, [&](uint32_t slot, uint32_t out) {
+        if (live) atomicAdd(&bins[out + slot], 1u);
+      });
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < ch.bins; i += kWalkThreads) {
+    const uint32_t v = bins[i];
+    if (v) atomicAdd(&a.hist[ch.bin0 + i], v);
+  }
+}
+
+// Explained rows: a block takes R rows and one group of output columns, and
+// per chunk of the units those columns need: its workers compute the units'
+// table slots into LDS (one pattern row of R slots per unit, a worker a tree's
+// segment at a time), then sum each column's entries in unit order, one column
+// per worker at a time, the reads of kWalkBatch entries in flight.  A worker is
+// R lanes, one per row: a whole wave for 64 rows (ops and entries are then
+// read through the scalar cache), 64 / R workers per wave for few rows, which
+// would leave most lanes idle and the workers' serial chains 64 / R times as
+// long (one row of the 100-tree depth-6 model: 49 us with 64-row tiles).  The
+// entries' order is that of the generated explain kernel's adds, so the sums
+// have the same bits.  No scratch outside LDS: calls on any streams may
+// overlap.
+template <typename PT, int ESHIFT, int R>
+__global__ __launch_bounds__(kWalkThreads) void k_walk(const WalkArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t wsmem[];
+  constexpr int W = kWalkThreads / R;  // workers
+  const int r = threadIdx.x & (R - 1);
+  const int worker = R == 64 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64) : (int)threadIdx.x / R;
+  PT *pat = (PT *)wsmem + r;
+  uint32_t *xt = a.x_off >= 0 ? wsmem + a.x_off / 4 : nullptr;
+  const int64_t row0 = (int64_t)blockIdx.x * R, row = row0 + r, rr = row < a.n ? row : a.n - 1;
+  const bool live = row < a.n;
+  const WalkGroup g = a.groups[blockIdx.y];
+  float *out = a.out + g.col0 * a.ldo + row;
+  if (xt) walk_load_tile<R>(a.X, a.ldx, row0, a.n, a.F, xt);
+  for (int c = g.chunk0; c < g.chunk1; ++c) {
+    const WalkChunk ch = a.chunks[c];
+    __syncthreads();  // the keys are stored; the last chunk's patterns (and its sums, in memory) are read
+    for (int s = ch.seg0 + worker; s < ch.seg1; s += W)
+      walk_segment<R>(a.ops, a.segs[s], a.X, a.ldx, rr, xt ? xt + r : nullptr,
+                      [&](uint32_t slot, uint32_t o) { pat[o * R] = (PT)slot; });
+    __syncthreads();
+    const bool first = c == g.chunk0;
+    for (int q = ch.run0 + worker; q < ch.run1; q += W) {
+      const WalkRun run = a.runs[q];
+      if (first && live)
+        for (int j = run.zero0; j < run.col; ++j) out[(int64_t)j * a.ldo] = 0.f;
+      if (run.e0 >= run.e1) continue;
+      float *dst = out + (int64_t)run.col * a.ldo;
+      float acc = !first && live ? *dst : 0.f;
+      for (int e = run.e0; e < run.e1; e += kWalkBatch) {
+        WalkEntry en[kWalkBatch];
+        float v[kWalkBatch];
+#pragma unroll
+        for (int u = 0; u < kWalkBatch; ++u) en[u] = a.entries[min(e + u, run.e1 - 1)];  // past the end: not added
+#pragma unroll
+        for (int u = 0; u < kWalkBatch; ++u) {
+          const uint32_t p = pat[(en[u].slot4 >> 2) * R];
+          const char *t = (const char *)a.tab + ((int64_t)en[u].tab16 << 4) + ((en[u].slot4 & 3u) << 2);
+          v[u] = *(const float *)(t + (p << ESHIFT));
+        }
+#pragma unroll
+        for (int u = 0; u < kWalkBatch; ++u)
+          if (e + u < run.e1) acc += v[u];
+      }
+      if (live) *dst = acc;
     }
   }
 }
@@ -380,20 +493,45 @@ __global__ __launch_bounds__(256) void k_pd_freq(const Group *__restrict__ group
 // Launchers
 // ---------------------------------------------------------------------------
 
-hipError_t launch_hist_generic(const Group *groups, const PathNode *path, int64_t n_groups, const float *B,
-                               int64_t m, int64_t ldb, uint32_t *hist, hipStream_t s) {
-  if (m <= 0 || n_groups <= 0) return hipSuccess;
-  dim3 grid((unsigned)((m + 255) / 256), (unsigned)((n_groups + kGroupsPerBlock - 1) / kGroupsPerBlock));
-  hipLaunchKernelGGL(k_hist_generic, grid, dim3(256), 0, s, groups, path, n_groups, B, m, ldb, hist);
+namespace {
+using WalkKernel = void (*)(const WalkArgs);
+// [pattern rows and entry stride][rows per block: 1, 4, 16, 64]
+const WalkKernel kWalkKernels[3][4] = {
+    {k_walk<uint8_t, 4, 1>, k_walk<uint8_t, 4, 4>, k_walk<uint8_t, 4, 16>, k_walk<uint8_t, 4, 64>},
+    {k_walk<uint16_t, 4, 1>, k_walk<uint16_t, 4, 4>, k_walk<uint16_t, 4, 16>, k_walk<uint16_t, 4, 64>},
+    {k_walk<uint8_t, 2, 1>, k_walk<uint8_t, 2, 4>, k_walk<uint8_t, 2, 16>, k_walk<uint8_t, 2, 64>}};
+}  // namespace
+
+hipError_t walk_init() {
+  // dynamic LDS past 64 KB has to be asked for
+  const int most = 160 * 1024;
+  hipError_t e = hipFuncSetAttribute((const void *)k_hist_walk, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+  for (const auto &kind : kWalkKernels)
+    for (WalkKernel f : kind)
+      if (e == hipSuccess) e = hipFuncSetAttribute((const void *)f, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+  return e;
+}
+
+hipError_t launch_hist_walk(const HistWalkArgs &a, hipStream_t s) {
+  if (a.m <= 0 || (a.n_chunks <= 0 && a.n_root_bins <= 0)) return hipSuccess;
+  const int64_t tiles = (a.m + 63) / 64;
+  // two blocks per CU over all chunks, at most one per tile
+  const int64_t per = (2 * (int64_t)a.n_cu + a.n_chunks - 1) / a.n_chunks;
+  const size_t lds = (size_t)kHistWalkBins * 4 + (a.F <= kWalkXFeatures ? (size_t)a.F * 256 : 0);
+  hipLaunchKernelGGL(k_hist_walk, dim3((unsigned)(per < tiles ? per : tiles), (unsigned)a.n_chunks),
+                     dim3(kWalkThreads), lds, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_explain_generic(const Group *groups, const PathNode *path, int64_t n_groups, const float *tab,
-                                  const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, int F,
-                                  hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_explain_generic, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, groups, path,
-                     n_groups, tab, X, n, ldx, phi, ldphi, F);
+hipError_t launch_walk(WalkArgs a, int n_groups, int max_slots, bool wide, int entry_shift, int rows, hipStream_t s) {
+  if (a.n <= 0 || n_groups <= 0) return hipSuccess;
+  if ((entry_shift != 4 && (entry_shift != 2 || wide)) || (rows != 1 && rows != 4 && rows != 16 && rows != 64))
+    return hipErrorInvalidValue;
+  size_t lds = ((size_t)max_slots * rows * (wide ? 2 : 1) + 15) / 16 * 16;
+  a.x_off = a.F <= kWalkXFeatures ? (int)lds : -1;
+  if (a.x_off >= 0) lds += (size_t)a.F * rows * 4;
+  const WalkKernel f = kWalkKernels[entry_shift == 2 ? 2 : wide ? 1 : 0][rows == 1 ? 0 : rows == 4 ? 1 : rows == 16 ? 2 : 3];
+  hipLaunchKernelGGL(f, dim3((unsigned)((a.n + rows - 1) / rows), (unsigned)n_groups), dim3(kWalkThreads), lds, s, a);
   return hipGetLastError();
 }
 

@@ -121,7 +121,7 @@ extern "C" int wdf_model_autotune(wdf_model *M, const float *B, int64_t m, int64
     if ((rc = jit_build(M))) return;
     wdf_bg *bg = nullptr;
     if ((rc = wdf_background_load(M, B, m, ldb, 1, WDF_SHAPLEY, s, &bg))) return;
-    ms = time_runs(s, reps, [&] { return wdf_explain(bg, X, n, ldx, phi.as<float>(), n, s); }, rc);
+    ms = time_runs(s, reps, [&] { return jit_explain(bg, X, n, ldx, phi.as<float>(), n, s); }, rc);
     wdf_bg_destroy(bg);
   };
   {
