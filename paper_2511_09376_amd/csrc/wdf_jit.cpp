@@ -395,7 +395,7 @@ struct Gen {
   }
 
   std::function<void(int64_t unit, const std::string &p)> on_quad;  // null: no quads
-  std::function<void()> on_tree_end;                                 // before a tree's block closes
+  const char *tree_block = "if (live) {\n";  // opens a tree's block
 
   void test(int64_t nd, const std::string &pout, const std::string &pin) {
     const int f = M->feature[(size_t)nd];
@@ -468,9 +468,8 @@ struct Gen {
       if (M->feature[(size_t)root] < 0) continue;
       // `live` is always 1; the branch only splits the code into one basic
       // block per tree, which keeps instruction selection time linear
-      o << "if (live) {\n";
+      o << tree_block;
       node(root, "zero");
-      if (on_tree_end) on_tree_end();
       o << "}\n";
     }
   }
@@ -779,9 +778,23 @@ const char *kStagePieceBuf = R"(
 #define STAGE_PIECE_B(sofs, dst, c) \
   __builtin_amdgcn_raw_ptr_buffer_load_lds(trs, (__attribute__((address_space(3))) void*)((dst) + 4 * (c) + wbase4), \
                                            16, tvoff, (sofs) + 16 * (c), 0, 0)
+// the same by one quarter of the block's waves (piece c + thread of the quarter)
+#define STAGE_QUARTER(sofs, dst, c) \
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(trs, (__attribute__((address_space(3))) void*)((dst) + 4 * (c) + qbase4), \
+                                           16, qvoff, (sofs) + 16 * (c), 0, 0)
 )";
 
-constexpr int kGatherBatch = 4;  // explain units whose table reads are in flight together
+// Table reads (16 bytes) the explain kernel issues together.  Two batches'
+// values and about 40 other registers have to fit the 256 registers of two
+// waves per SIMD beside a row's accumulators and rank words (127 features, 32
+// words: 228 registers with batches of six reads).
+constexpr int kGatherReads = 6, kGatherUnits = 3;
+int gather_reads(int accumulators, int words) {
+  return accumulators + words <= 160 ? kGatherReads : accumulators + words <= 185 ? 4 : 2;
+}
+// Explain tables larger than this are prefetched into the XCD's L2 (4 MB,
+// shared with the instructions and the rows) one stage before their copy.
+constexpr int64_t kL2PrefetchBytes = 2 << 20;
 
 // Unrolled copy of n16 16-byte pieces from tab + t0 to LDS at dst_off floats:
 // full chunks of nt pieces unconditionally, the last one for the threads it covers.
@@ -818,20 +831,32 @@ std::string gen_explain(const wdf_model *M, const TreeIndex &ix) {
     << "typedef const __attribute__((address_space(3))) vf4* lvf4;  // an LDS address (32 bits)\n"
     << "// a table component that adds to no feature (a zero): used by an empty asm,\n"
     << "// so that the read stays 16 bytes wide without an instruction for it\n"
-    << "#define KEEP(v) asm volatile(\"\" :: \"v\"(v))\n";
+    << "#define KEEP(v) asm volatile(\"\" :: \"v\"(v))\n"
+    << "// ends a basic block, without a value that differs between the two ways on\n"
+    << "#define SPLIT() do { asm volatile(\"\" : \"+s\"(on)); if (!on) asm volatile(\"\"); } while (0)\n";
   // stage copies through a buffer descriptor while the tables' byte offsets
   // fit its 31-bit size (every realistic model), else global addresses
   const bool buf_copy = 4 * P.xtab_size <= 0x7fffffffll;
   auto copy = buf_copy ? emit_stage_copy_buf : emit_stage_copy;
+  o << "__constant__ const " << (buf_copy ? "u32" : "i64") << " stage_at[] = {";  // first float of every stage, and the end
+  for (const auto &st : P.explain_stages) {
+    size_t u = 0;
+    while (P.unit_g0[u] != st.first) ++u;
+    o << P.xunits[u].dst << ", ";
+  }
+  o << P.xtab_size << "};\n";
   o << (buf_copy ? kStagePieceBuf : kStagePiece) << R"(// one row per lane, one tile of NT rows per block
 extern "C" __global__ __launch_bounds__(NT, 2) void EXPLAIN_NAME(const float* __restrict__ X, i64 ldx,
                                                                      const float* __restrict__ tab,
                                                                      const float* __restrict__ thr,
-                                                                     float* __restrict__ phi, i64 ldphi, i64 n, int live) {
+                                                                     float* __restrict__ phi, i64 ldphi, i64 n, int rows) {
   __shared__ __attribute__((aligned(16))) float lds[2 * SF];
+  // the block takes `rows` rows (a multiple of 64, at most NT); waves past them only copy
+  const int live = (int)__builtin_amdgcn_readfirstlane(threadIdx.x) < rows;
+  int on = 1;  // always
   const u32 zero = 0u;
   const u32 wbase4 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u) * 4u;  // the wave's first piece, in floats
-  const i64 row = (i64)blockIdx.x * NT + threadIdx.x;
+  const i64 row = (i64)blockIdx.x * rows + threadIdx.x;
   const i64 rr = row < n ? row : n - 1;
 )";
   if (buf_copy)
@@ -863,95 +888,271 @@ extern "C" __global__ __launch_bounds__(NT, 2) void EXPLAIN_NAME(const float* __
     if (used[(size_t)f]) o << "  float f" << f << " = 0.f;\n";
   if (P.thr_in_lds && !thr_hi) o << "  __syncthreads();\n";  // every wave is done with the thresholds
   if (!thr_hi) copy(o, t0, 0, n16, P.nt_explain);
-  o << "  __builtin_amdgcn_s_waitcnt(0);\n  __syncthreads();\n";
   o << "  LDS_BASES\n";
   std::set<int64_t> lds_bases;  // 32 KiB steps of the LDS the gathers address from a base register
-  for (size_t s = 0; s < S.size(); ++s) {
-    const int buf = (int)(s & 1);
-    if (s + 1 < S.size()) {
-      stage_span(s + 1, t0, n16);
-      copy(o, t0, (int64_t)(1 - buf) * P.stage_floats, n16, P.nt_explain);
+
+  // The units in order, in batches of units of one stage (gather_reads)
+  // whose table reads are issued together.  The kernel is one software
+  // pipeline over the batches, across trees and stages: step k issues batch
+  // k's reads, adds batch k - 1's values and computes batch k + 1's slots, so
+  // the reads' latency is covered by vector work and, at a stage's barrier,
+  // the next stage's first slots are already there and the last batch's adds
+  // still to do.  With the work of a stage confined to it (slots, reads, adds,
+  // barrier), all waves ran the vector-only and the LDS-only ends of a stage
+  // together: about 750 cycles of every barrier.
+  // What bounds it (paper shape, 3M rows): the LDS, 23 block waves x (228k
+  // cycles of table reads + ~80k of stage copies) = 2.95 ms at 2.4 GHz; the
+  // VALU has 2.3 ms of work.  4.26 ms with stages confined, 4.09 pipelined,
+  // 3.45 with the copies by quarters, the priorities, the L2 prefetch and
+  // the waves' own blocks below (without any barrier, computing wrong values,
+  // 3.2).  100 uneven trees, 300k rows: 0.703 -> 0.586 ms.
+  struct Event {
+    std::string tests, slot;      // code that computes the slot, and the slot's name
+    const XUnit *x;
+    std::vector<const PathNode *> pos;  // path node of every value
+    size_t stage;
+  };
+  std::vector<Event> ev;
+  std::vector<int64_t> event_of(P.xunits.size(), -1);
+  std::vector<size_t> batch0;  // first event of every batch
+  const int max_reads = gather_reads((int)std::count(used.begin(), used.end(), (char)1), P.words);
+  {
+    size_t s = 0;
+    int open_reads = 0;
+    for (size_t u = 0; u < P.xunits.size(); ++u) {
+      const Group &g = M->groups[(size_t)P.unit_g0[u]];
+      while (P.unit_g0[u] >= S[s].second) ++s;
+      if (g.depth == 0) continue;
+      const int planes = (P.xunits[u].nv + 3) / 4;
+      if (ev.empty() || ev.back().stage != s || open_reads + planes > max_reads ||
+          ev.size() - batch0.back() == (size_t)kGatherUnits) {
+        batch0.push_back(ev.size());
+        open_reads = 0;
+      }
+      open_reads += planes;
+      Event e;
+      e.x = &P.xunits[u];
+      for (int v = 0; v < g.depth; ++v) e.pos.push_back(&M->path[(size_t)g.path_off + v]);
+      if (e.x->quad) {
+        const Group &gr = M->groups[(size_t)P.unit_g0[u] + 1];
+        e.pos.push_back(&M->path[(size_t)gr.path_off + gr.depth - 1]);
+      }
+      e.stage = s;
+      event_of[u] = (int64_t)ev.size();
+      ev.push_back(std::move(e));
     }
-    const int64_t sbase = P.xunits[(size_t)unit_of[(size_t)S[s].first]].dst;
-    // One 16-byte read per float4 plane returns four values of the entry;
-    // value v adds to the feature of its path position when that position is
-    // the feature's first on the path.  Components that add to no feature
-    // (zeros in the tables) are kept by an empty asm (KEEP), so that no read is
-    // narrowed to an 8- or 12-byte one (more LDS cycles per value on random
-    // addresses) and no instruction is spent on them.  The
-    // reads of kGatherBatch units are issued before their adds, with a
-    // scheduling barrier between, so that that many are in flight (the
-    // compiler otherwise reads, waits and adds one unit at a time).
-    std::string pending;  // adds of the units whose reads are issued
-    int npending = 0, greg = 0;
-    auto flush = [&]() {
-      if (!npending) return;
-      o << "__builtin_amdgcn_sched_barrier(0);\n" << pending;
-      pending.clear();
-      npending = 0;
+  }
+  const size_t NB = batch0.size();
+  batch0.push_back(ev.size());
+  // the tests, cut at the units
+  {
+    std::ostringstream keep;
+    keep << o.str();
+    o.str("");
+    auto cut = [&](int64_t u, const std::string &pidx) {
+      const XUnit &x = P.xunits[(size_t)u];
+      Event &e = ev[(size_t)event_of[(size_t)u]];
+      e.slot = gen.slot(pidx, x.depth + x.quad, x.fold_a, x.fold_b);
+      e.tests = o.str();
+      o.str("");
     };
-    auto gather = [&](const XUnit &x, const std::string &pidx, const std::vector<const PathNode *> &pos) {
+    gen.on_group = [&](int64_t g, const std::string &p) { cut(unit_of[(size_t)g], p); };
+    gen.on_quad = cut;
+    gen.tree_block = "SPLIT();\n{\n";
+    if (!M->groups.empty()) gen.range(0, (int64_t)M->groups.size());
+    o.str("");  // the end of the last tree's block
+    o << keep.str();
+  }
+  // values read and slots, one set of variables per batch (one set for all
+  // would make each of them a single live range through the whole kernel,
+  // which the compiler takes minutes over)
+  for (size_t k = 0; k < NB; ++k) {
+    for (size_t i = batch0[k]; i < batch0[k + 1]; ++i) {
+      o << "  u32 s" << i << "; vf4";
+      for (int j = 0; 4 * j < ev[i].x->nv; ++j) o << (j ? ", r" : " r") << i << "_" << j;
+      o << ";\n";
+    }
+  }
+  // pieces of a step
+  auto tests = [&](size_t k) {
+    for (size_t i = batch0[k]; i < batch0[k + 1]; ++i)
+      o << ev[i].tests << "s" << i << " = " << ev[i].slot << ";\n";
+  };
+  int greg = 0;
+  std::vector<std::string> adds(2);
+  // One 16-byte read per float4 plane returns four values of the entry; value v
+  // adds to the feature of its path position when that position is the
+  // feature's first on the path.  Components that add to no feature (zeros in
+  // the tables) are kept by an empty asm (KEEP), so that no read is narrowed
+  // to an 8- or 12-byte one (more LDS cycles per value on random addresses)
+  // and no instruction is spent on them.
+  auto reads = [&](size_t k) {
+    std::ostringstream add;
+    std::set<int32_t> sums;
+    for (size_t i = batch0[k]; i < batch0[k + 1]; ++i) {
+      const Event &e = ev[i];
+      const XUnit &x = *e.x;
       const int64_t E = (int64_t)1 << (x.depth + x.quad);
-      const std::string p = gen.slot(pidx, x.depth + x.quad, x.fold_a, x.fold_b);
+      const int64_t sbase = P.xunits[(size_t)unit_of[(size_t)S[e.stage].first]].dst;
+      const std::string p = "s" + std::to_string(i);
       static const char *C[4] = {"x", "y", "z", "w"};
-      std::ostringstream adds;
       for (int j = 0; 4 * j < x.nv; ++j) {
         bool any = false;
-        for (int c = 0; c < 4 && 4 * j + c < x.nv; ++c) any = any || pos[(size_t)(4 * j + c)]->first;
+        for (int c = 0; c < 4 && 4 * j + c < x.nv; ++c) any = any || e.pos[(size_t)(4 * j + c)]->first;
         if (!any) continue;
         const std::string gv = "g" + std::to_string(greg++);
+        const std::string reg = "r" + std::to_string(i) + "_" + std::to_string(j);
         // ds_read's offset field holds 16 bits: a unit whose last plane ends
         // past 64 KiB is addressed from the opaque base below it (lb<k>: LDS
         // byte offset k * 32 KiB), so its address stays one shift-add
-        const int64_t ofs = buf * P.stage_floats + (x.dst - sbase);  // floats
+        const int64_t ofs = (int64_t)(e.stage & 1) * P.stage_floats + (x.dst - sbase);  // floats
         const int64_t last_end = 4 * (ofs + 4 * (int64_t)((x.nv + 3) / 4 - 1) * E + 4 * E);
         if (last_end <= 65536) {
-          o << "const vf4 " << gv << " = ((const vf4*)(lds + " << ofs << ") + " << p << ")[" << j * E << "];\n";
+          o << "const vf4 " << gv << " = ((const vf4*)(lds + " << ofs << ") + " << p << ")[" << j * E << "]; ";
         } else {
-          const int64_t k = 4 * ofs / 32768;
-          lds_bases.insert(k);
-          o << "const vf4 " << gv << " = (lb" << k << " + " << (ofs - k * 8192) / 4 << " + " << p << ")[" << j * E
-            << "];\n";
+          const int64_t b = 4 * ofs / 32768;
+          lds_bases.insert(b);
+          o << "const vf4 " << gv << " = (lb" << b << " + " << (ofs - b * 8192) / 4 << " + " << p << ")[" << j * E
+            << "]; ";
         }
+        o << reg << " = " << gv << ";\n";
+        add << "{ vf4 " << gv << " = " << reg << ";";
         for (int c = 0; c < 4; ++c) {
-          const bool real = 4 * j + c < x.nv && pos[(size_t)(4 * j + c)]->first;
-          if (real) adds << " f" << pos[(size_t)(4 * j + c)]->feat << " += " << gv << "." << C[c] << ";";
-          else adds << " KEEP(" << gv << "." << C[c] << ");";
+          const bool real = 4 * j + c < x.nv && e.pos[(size_t)(4 * j + c)]->first;
+          if (real) {
+            const int32_t f = e.pos[(size_t)(4 * j + c)]->feat;
+            add << " f" << f << " += " << gv << "." << C[c] << ";";
+            sums.insert(f);
+          } else add << " KEEP(" << gv << "." << C[c] << ");";
         }
+        add << " }\n";
       }
-      pending += adds.str() + "\n";
-      if (++npending == kGatherBatch) flush();
-    };
-    gen.on_tree_end = flush;
-    gen.on_group = [&](int64_t g, const std::string &p) {
-      const Group &gr = M->groups[(size_t)g];
-      std::vector<const PathNode *> pos;
-      for (int k = 0; k < gr.depth; ++k) pos.push_back(&M->path[(size_t)gr.path_off + k]);
-      gather(P.xunits[(size_t)unit_of[(size_t)g]], p, pos);
-    };
-    gen.on_quad = [&](int64_t u, const std::string &p) {
-      const XUnit &x = P.xunits[(size_t)u];
-      const Group &gl = M->groups[(size_t)P.unit_g0[(size_t)u]], &gr = M->groups[(size_t)P.unit_g0[(size_t)u] + 1];
-      std::vector<const PathNode *> pos;
-      for (int v = 0; v < x.depth; ++v) pos.push_back(&M->path[(size_t)gl.path_off + v]);
-      pos.push_back(&M->path[(size_t)gr.path_off + x.depth - 1]);
-      gather(x, p, pos);
-    };
-    o << "  {\n";
-    gen.range(S[s].first, S[s].second);
-    o << "  }\n";
-    // keep each stage's accumulations inside the stage: without this the adds
-    // sink to the final (conditional) stores and every gathered value stays live
-    std::vector<char> touched((size_t)F, 0);
-    for (int64_t g = S[s].first; g < S[s].second; ++g) {
-      const Group &gr = M->groups[(size_t)g];
-      for (int k = 0; k < gr.depth; ++k)
-        if (M->path[(size_t)gr.path_off + k].first) touched[(size_t)M->path[(size_t)gr.path_off + k].feat] = 1;
     }
-    for (int f = 0; f < F; ++f)
-      if (touched[(size_t)f]) o << "  asm volatile(\"\" : \"+v\"(f" << f << "));\n";
-    if (s + 1 < S.size()) o << "  __builtin_amdgcn_s_waitcnt(0);\n  __syncthreads();\n";
+    // the sums are used here, so that they are formed here: left alone the
+    // compiler moves adds down (to the tree's end, or to the final stores) and
+    // keeps the values read live
+    const char *sep = "asm volatile(\"\" :: ";
+    for (int32_t f : sums) {
+      add << sep << "\"v\"(f" << f << ")";
+      sep = ", ";
+    }
+    if (!sums.empty()) add << ");\n";
+    adds[k & 1] = add.str();
+  };
+  auto add_batch = [&](size_t k) { o << adds[k & 1]; };
+  const char *kSched = "__builtin_amdgcn_sched_barrier(0);\n";
+  size_t done = 0;  // stages whose barrier is passed
+  auto enter = [&](size_t s) {  // the tables of stage s are in LDS, all waves are done with stage s - 1
+    o << "  __builtin_amdgcn_s_waitcnt(0);\n  __syncthreads();\n";
+    done = s + 1;
+  };
+  // The copy of stage s, in quarters: a quarter of the waves copies a quarter
+  // of the stage, at the first four steps of the stage before.  A copy
+  // instruction holds its wave until the CU's address unit takes it (ten per
+  // wave and 80 KB stage); with all waves copying at a stage's start they all
+  // stood there together, with the vector units and the LDS idle (paper shape
+  // 4.09 ms at once, 3.79 in two halves, 3.74 in quarters).
+  // Models of more stages copy at once: the compiler's time grows with the
+  // square of the copies' number (the 500-tree ensemble's 640 stages).
+  const int NQ = P.nt_explain / 4;
+  const bool by_quarters = buf_copy && S.size() <= 256;
+  std::vector<std::string> quarters;  // of the stage being copied, not yet issued
+  auto start_copy = [&](size_t s) {
+    if (s >= S.size()) return;
+    stage_span(s, t0, n16);
+    if (!by_quarters) {
+      copy(o, t0, (int64_t)(s & 1) * P.stage_floats, n16, P.nt_explain);
+      return;
+    }
+    for (int q = 3; q >= 0; --q) {
+      const int64_t c0 = n16 * q / 4 / NQ * NQ, c1 = q == 3 ? n16 : n16 * (q + 1) / 4 / NQ * NQ;
+      if (c0 == c1) continue;
+      std::ostringstream w;
+      w << "  if (quarter == " << q << "u) { float* d_ = lds + " << (int64_t)(s & 1) * P.stage_floats << ";";
+      for (int64_t c = c0; c < c1; c += NQ) {
+        if (c1 - c < NQ) w << " if (qthread < " << c1 - c << "u)";
+        w << " STAGE_QUARTER(" << 4 * t0 << "u, d_, " << c << "u);";
+      }
+      w << " }\n";
+      quarters.push_back(w.str());
+    }
+  };
+  auto copy_quarter = [&] {
+    if (quarters.empty()) return;
+    o << quarters.back();
+    quarters.pop_back();
+  };
+  // Lines of the stage after next into the L2, each by one of the (up to) 32
+  // blocks an XCD runs side by side: the tables pass through the L2 once per
+  // block wave and, when larger than it, are in the last-level cache when the
+  // copies ask for them (paper shape 3.74 -> 3.68 ms, 100 uneven trees 0.637 ->
+  // 0.613 ms; with every block prefetching all lines it was slower than none).
+  const bool l2_prefetch = by_quarters && 4 * P.xtab_size > kL2PrefetchBytes;
+  auto prefetch_l2 = [&](size_t s) {
+    if (!l2_prefetch || s >= S.size()) return;
+    stage_span(s, t0, n16);
+    o << "  KEEP(pf); pf = __builtin_amdgcn_raw_buffer_load_b32(trs, pfoff, " << 4 * t0 << "u, 0);\n";
+  };
+  if (by_quarters)
+    o << "  const u32 qthread = threadIdx.x & " << NQ - 1 << "u, qvoff = qthread * 16u;\n"
+      << "  const u32 quarter = __builtin_amdgcn_readfirstlane(threadIdx.x / " << NQ << "u);\n"
+      << "  const u32 qbase4 = wbase4 & " << 4 * NQ - 1 << "u;  // the wave's first piece of its quarter, in floats\n";
+  if (l2_prefetch) {
+    const int waves = P.nt_explain / 64;
+    const int lanes = (P.stage_floats * 4 + 128 * 32 * waves - 1) / (128 * 32 * waves);
+    o << "  u32 pf = 0u;\n"
+      << "  const u32 pfoff = (threadIdx.x & 63u) < " << lanes << "u ? (((threadIdx.x & 63u) * " << waves
+      << "u + (threadIdx.x >> 6)) * 32u + ((blockIdx.x >> 3) & 31u)) * 128u : 0x80000000u;  // past the tables: no access\n";
   }
+  o << "  if (live) {\n";
+  if (NB) tests(0);
+  size_t step0 = 0;  // first step of the stage
+  for (size_t k = 0; k < NB; ++k) {
+    const size_t s = ev[batch0[k]].stage;
+    bool fresh = false;
+    while (done <= s) {  // (stages without a read are passed over)
+      while (!quarters.empty()) copy_quarter();
+      enter(done);
+      fresh = true;
+      if (done <= s) start_copy(done);
+    }
+    if (fresh) {
+      step0 = k;
+      start_copy(s + 1);
+    }
+    size_t step1 = k + 1;
+    while (step1 < NB && ev[batch0[step1]].stage == s) ++step1;
+    // the wave that is behind in its stage goes first: left alone the older
+    // wave of a SIMD runs ahead and the younger one finishes the stage by
+    // itself (paper shape 3.79 -> 3.74 ms)
+    o << "__builtin_amdgcn_s_setprio(" << 3 - 4 * (k - step0) / (step1 - step0) << ");\n";
+    reads(k);
+    o << kSched;
+    copy_quarter();
+    if (fresh) prefetch_l2(s + 2);
+    if (k) add_batch(k - 1);
+    if (k + 1 < NB) tests(k + 1);
+    o << kSched;
+  }
+  if (NB) {
+    add_batch(NB - 1);
+    o << "}\n";  // the last tree's block
+  }
+  // waves without rows: the same barriers and their share of the copies, as a
+  // loop (little code to fetch beside the other waves')
+  o << "  } else {\n    for (u32 s = 0; s < " << done << "u; ++s) {\n"
+    << "      __builtin_amdgcn_s_waitcnt(0);\n      __syncthreads();\n      if (s + 1u >= " << S.size() << "u) continue;\n"
+    << "      const "
+    << (buf_copy ? "u32" : "i64") << " b = stage_at[s + 1u]; const u32 n16 = (u32)(stage_at[s + 2u] - b) / 4u;  // floats, 16-byte pieces\n"
+    << "      float* d_ = lds + ((s + 1u) & 1u) * SF;\n";
+  if (by_quarters)
+    o << "      const u32 c1 = quarter == 3u ? n16 : n16 * (quarter + 1u) / 4u / " << NQ << "u * " << NQ << "u;\n"
+      << "      for (u32 c = n16 * quarter / 4u / " << NQ << "u * " << NQ << "u; c < c1; c += " << NQ
+      << "u)\n        if (c + qthread < c1) STAGE_QUARTER(4u * b, d_, c);\n";
+  else
+    o << "      for (u32 c = 0; c < n16; c += NT)\n        if (c + threadIdx.x < n16) "
+      << (buf_copy ? "STAGE_PIECE_B(4u * b, d_, c);\n" : "STAGE_PIECE(tab + b, d_, c);\n");
+  o << "    }\n  }\n";
   {
     // opaque base registers (the compiler would otherwise rebuild each
     // constant address past 64 KiB with an extra move)
@@ -964,7 +1165,7 @@ extern "C" __global__ __launch_bounds__(NT, 2) void EXPLAIN_NAME(const float* __
     o.str("");
     o << body;
   }
-  o << "  if (row < n) {\n";
+  o << "  if (live && row < n) {\n";
   // phi is written once per launch and not read back: non-temporal stores
   for (int f = 0; f < F; ++f)
     o << "    __builtin_nontemporal_store(" << (used[(size_t)f] ? "f" + std::to_string(f) : "0.f") << ", &phi[" << f
@@ -1693,9 +1894,14 @@ int jit_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float 
   const JitPlan &P = M->jp;
   const float *tab = bg->d_xtab.as<float>();
   const float *thr = P.d_thr_pad.as<float>();
-  int live = 1;
-  void *args[] = {(void *)&X, &ldx, (void *)&tab, (void *)&thr, &phi, &ldphi, &n, &live};
-  const unsigned blocks = (unsigned)((n + P.nt_explain - 1) / P.nt_explain);
+  // Rows per block: a full tile once every CU has one, else the rows spread
+  // over all CUs in whole waves (a block's time falls with its rows: 20 000
+  // rows of the 100-tree depth-6 model 187 us in 40 blocks of 512, 147 us in
+  // 157 of 128; 100 000 rows 198 -> 170 us with the kernel's pipeline).
+  const int64_t slots = (int64_t)M->ctx->n_cu * P.explain_bpc;
+  int rows = (int)std::min<int64_t>(P.nt_explain, ((n + slots - 1) / slots + 63) / 64 * 64);
+  void *args[] = {(void *)&X, &ldx, (void *)&tab, (void *)&thr, &phi, &ldphi, &n, &rows};
+  const unsigned blocks = (unsigned)((n + rows - 1) / rows);
   hipError_t e = hipModuleLaunchKernel(M->jit->explain, blocks, 1, 1, (unsigned)P.nt_explain, 1, 1, 0, s, args, nullptr);
   if (e != hipSuccess) return hip_error(e, "hipModuleLaunchKernel(explain)");
   return WDF_OK;
