@@ -576,6 +576,7 @@ static int iv_layout_host(wdf_model *M, std::vector<int32_t> &ioff, std::vector<
       while ((items.size() / 2) % 8) items.insert(items.end(), {(int32_t)M->iv_tab_size, l.back()[0]});
     ioff[(size_t)f + 1] = (int32_t)(items.size() / 2);
   }
+  M->iv_values = (int64_t)items.size() / 2;
   if (items.empty()) items.assign(2, 0);
   // Units of the interleaved tables (specialised kernel): per feature i,
   // one per group where i has a first occurrence and a partner, in group
@@ -638,6 +639,7 @@ static int prepare_iv(wdf_model *M, int kind) {
     if ((rc = upload(M->d_siv_class_off, soff, s))) return rc;
     if ((rc = upload(M->d_iv_item_off, ioff, s))) return rc;
     if ((rc = upload(M->d_iv_items, items, s))) return rc;
+    if ((rc = walk_build_iv(M))) return rc;
     M->iv_layout = true;
   }
   if (!M->iv_coef_ready[kind]) {
@@ -999,7 +1001,9 @@ extern "C" int wdf_explain_iv(const wdf_bg *bg, const float *X, int64_t n, int64
   if ((uintptr_t)workspace % 16)
     return set_error(WDF_E_INVALID_ARG, "wdf_explain_iv: workspace not 16-byte aligned");
   hipStream_t s = pick_stream(M->ctx, hip_stream);
-  if (bg->iv_spec) return jit_explain_iv(bg, X, ldx, (uint8_t *)workspace, n, iv, ldiv, s);
+  const int64_t work = n * M->iv_values;
+  if (M->walk_iv && (n <= kWalkIvRows || work <= kWalkIvWork)) return walk_explain_iv(bg, X, n, ldx, iv, ldiv, s);
+  if (bg->iv_spec && work > iv_generic_work(M->n_nodes)) return jit_explain_iv(bg, X, ldx, (uint8_t *)workspace, n, iv, ldiv, s);
   HIP_TRY(launch_explain_iv(M->d_groups.as<Group>(), M->d_path.as<PathNode>(), G, M->d_iv_item_off.as<int32_t>(),
                             M->d_iv_items.as<int2>(), bg->d_tab.as<float>(), X, n, ldx, (uint8_t *)workspace, iv, ldiv,
                             M->n_features, s));

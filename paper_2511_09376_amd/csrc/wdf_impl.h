@@ -103,6 +103,17 @@ struct WalkHist {
 // tables through the LDS of every CU it uses, a fixed time; the gather's time
 // grows with the rows once its blocks fill the device.
 constexpr int64_t kWalkMaxRows = 2048;
+// Interaction values of n rows: the data-driven gather (no pattern pass, one
+// launch) for few rows or little work (rows x table values added per row), then
+// the generic kernels (two launches) up to iv_generic_work, then the generated
+// ones (a pattern pass that walks all trees in one thread per row, and a kernel
+// per four features, over four streams).  Measured, us, gather / generic /
+// generated: 20 depth-6 trees of 127 features, 64 rows 19 / 47 / 163, 512 rows
+// 53 / 65 / 160, 1024 rows 78 / 73 / 165, 6144 rows - / 177 / 196, 8192 rows
+// 446 / 235 / 199; 100 trees, 512 rows 133 / 150 / 427, 4096 rows 711 / 399 /
+// 445; 10 depth-4 trees of 8 features, 8192 rows 15 / - / 61.
+constexpr int64_t kWalkIvRows = 512, kWalkIvWork = 16 << 20;
+inline int64_t iv_generic_work(int64_t n_nodes) { return ((int64_t)56 << 20) + 27 * 1024 * n_nodes; }
 constexpr int kWalkPatternBytes = 32768;  // pattern rows of a chunk in LDS
 
 }  // namespace wdf
@@ -150,6 +161,7 @@ struct wdf_model {
   // with the explain-table units), and the generic models' histogram
   std::vector<std::unique_ptr<wdf::WalkLevel>> walk;
   wdf::WalkHist walk_hist;
+  std::unique_ptr<wdf::WalkLevel> walk_iv;  // interaction values of few rows (null: none)
 
   // workspace of background summaries (threshold codes, contraction columns
   // and products), grown on demand and reused; ws_mu serialises summaries of
@@ -174,6 +186,7 @@ struct wdf_model {
   std::vector<std::array<int32_t, 7>> iv_unit_partners;  // partner features of each unit
   std::vector<int32_t> iv_unit_off;
   int64_t iv_units_size = 0;   // floats
+  int64_t iv_values = 0;       // table values added per row, all columns
   wdf::DevBuf d_iv_units;
   bool iv_coef_ready[2] = {false, false};
   wdf::DevBuf d_coef_iv[2][WDF_MAX_DEPTH + 1];  // [Shapley/Banzhaf][dprime]
@@ -245,4 +258,6 @@ int walk_build_explain(wdf_model *M);
 int walk_build_hist(wdf_model *M);
 int walk_hist(const wdf_model *M, const float *B, int64_t m, int64_t ldb, uint32_t *hist, hipStream_t s);
 int walk_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, hipStream_t s);
+int walk_build_iv(wdf_model *M);
+int walk_explain_iv(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *iv, int64_t ldiv, hipStream_t s);
 }  // namespace wdf

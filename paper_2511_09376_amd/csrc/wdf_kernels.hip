@@ -40,7 +40,6 @@ __device__ __forceinline__ uint32_t group_pattern(const Group &g, const PathNode
 // CUs.
 
 constexpr int kWalkThreads = 512, kWalkWaves = kWalkThreads / 64;
-constexpr int kWalkBatch = 16;      // table entries in flight per lane
 constexpr int kWalkXFeatures = 160;  // row keys staged in LDS up to this many features (40 KB)
 
 __device__ __forceinline__ uint32_t walk_key(float x) { return walk_key_bits(__float_as_uint(x)); }
@@ -130,7 +129,7 @@ __global__ __launch_bounds__(kWalkThreads) void k_hist_walk(const HistWalkArgs a
 // per chunk of the units those columns need: its workers compute the units'
 // table slots into LDS (one pattern row of R slots per unit, a worker a tree's
 // segment at a time), then sum each column's entries in unit order, one column
-// per worker at a time, the reads of kWalkBatch entries in flight.  A worker is
+// per worker at a time, the reads of kBatch entries in flight.  A worker is
 // R lanes, one per row: a whole wave for 64 rows (ops and entries are then
 // read through the scalar cache), 64 / R workers per wave for few rows, which
 // would leave most lanes idle and the workers' serial chains 64 / R times as
@@ -142,6 +141,7 @@ template <typename PT, int ESHIFT, int R>
 __global__ __launch_bounds__(kWalkThreads) void k_walk(const WalkArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t wsmem[];
   constexpr int W = kWalkThreads / R;  // workers
+  constexpr int kBatch = ESHIFT == 4 ? 16 : 4;  // (an interaction column has few entries)
   const int r = threadIdx.x & (R - 1);
   const int worker = R == 64 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64) : (int)threadIdx.x / R;
   PT *pat = (PT *)wsmem + r;
@@ -166,19 +166,19 @@ __global__ __launch_bounds__(kWalkThreads) void k_walk(const WalkArgs a) {
       if (run.e0 >= run.e1) continue;
       float *dst = out + (int64_t)run.col * a.ldo;
       float acc = !first && live ? *dst : 0.f;
-      for (int e = run.e0; e < run.e1; e += kWalkBatch) {
-        WalkEntry en[kWalkBatch];
-        float v[kWalkBatch];
+      for (int e = run.e0; e < run.e1; e += kBatch) {
+        WalkEntry en[kBatch];
+        float v[kBatch];
 #pragma unroll
-        for (int u = 0; u < kWalkBatch; ++u) en[u] = a.entries[min(e + u, run.e1 - 1)];  // past the end: not added
+        for (int u = 0; u < kBatch; ++u) en[u] = a.entries[min(e + u, run.e1 - 1)];  // past the end: not added
 #pragma unroll
-        for (int u = 0; u < kWalkBatch; ++u) {
+        for (int u = 0; u < kBatch; ++u) {
           const uint32_t p = pat[(en[u].slot4 >> 2) * R];
           const char *t = (const char *)a.tab + ((int64_t)en[u].tab16 << 4) + ((en[u].slot4 & 3u) << 2);
           v[u] = *(const float *)(t + (p << ESHIFT));
         }
 #pragma unroll
-        for (int u = 0; u < kWalkBatch; ++u)
+        for (int u = 0; u < kBatch; ++u)
           if (e + u < run.e1) acc += v[u];
       }
       if (live) *dst = acc;

@@ -6,6 +6,8 @@
 #include <array>
 #include <cstring>
 #include <functional>
+#include <map>
+#include <memory>
 #include <vector>
 
 #include "wdf.h"
@@ -267,6 +269,43 @@ int walk_build_explain(wdf_model *M) {
 }
 
 int walk_build_hist(wdf_model *M) {
+// Interaction values: column (i, j) at i F + j, one group per feature i.  The
+// units are the groups' patterns (the interaction tables are indexed by them).
+int walk_build_iv(wdf_model *M) {
+  const int F = M->n_features;
+  M->walk_iv.reset();
+  if (F > 4096) return WDF_OK;  // the runs that clear F x F columns would be most of the plan
+  std::vector<WalkUnit> units(M->groups.size());
+  std::vector<std::map<int32_t, std::vector<ColumnEntry>>> lists((size_t)F);
+  for (size_t g = 0; g < M->groups.size(); ++g) {
+    const Group &gr = M->groups[g];
+    const int d = gr.depth;
+    if (d < 2) continue;
+    units[g] = group_unit(M, (int64_t)g, right_turns(M, gr));
+    for (int k1 = 0; k1 < d; ++k1) {
+      const PathNode &a = M->path[(size_t)gr.path_off + (size_t)k1];
+      for (int k2 = 0; k2 < d && a.first; ++k2) {
+        const PathNode &b = M->path[(size_t)gr.path_off + (size_t)k2];
+        if (k2 == k1 || !b.first) continue;
+        const int lo = std::min(k1, k2), hi = std::max(k1, k2), q = lo * (2 * d - lo - 1) / 2 + (hi - lo - 1);
+        lists[(size_t)a.feat][b.feat].push_back(ColumnEntry{(int32_t)g, M->iv_off[g] + ((int64_t)q << d)});
+      }
+    }
+  }
+  std::vector<ColumnGroup> groups;
+  for (int i = 0; i < F; ++i) {
+    ColumnGroup g{(int64_t)i * F, F, {}};
+    for (const auto &l : lists[(size_t)i]) g.lists.push_back({l.first, &l.second});
+    groups.push_back(std::move(g));
+  }
+  std::unique_ptr<WalkLevel> L(new WalkLevel());
+  const int rc = build_level(M, units, groups, false, 2, *L);
+  if (rc == WDF_E_UNSUPPORTED) return WDF_OK;
+  if (rc) return rc;
+  M->walk_iv = std::move(L);
+  return WDF_OK;
+}
+
   const int64_t G = (int64_t)M->groups.size();
   Programs prog(M);
   std::vector<WalkUnit> units((size_t)G);
@@ -317,10 +356,22 @@ int walk_hist(const wdf_model *M, const float *B, int64_t m, int64_t ldb, uint32
 }
 
 int walk_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, hipStream_t s) {
+// level L's columns for n rows: the fewest rows per block that stay within two
+// blocks per CU, else 64
+static int walk_launch(const wdf_model *M, const WalkLevel &L, const float *tab, const float *X, int64_t n, int64_t ldx,
+                       float *out, int64_t ldo, hipStream_t s) {
+  const int64_t blocks = 2 * (int64_t)M->ctx->n_cu;
+  int rows = 1;
+  while (rows < 64 && (n + rows - 1) / rows * L.n_groups > blocks) rows *= 4;
+  const WalkArgs a{X, ldx, n, out, ldo, tab, L.ops.as<WalkOp>(), L.segs.as<int2>(), L.groups.as<WalkGroup>(),
+                   L.chunks.as<WalkChunk>(), L.runs.as<WalkRun>(), L.entries.as<WalkEntry>(), M->n_features, 0};
+  HIP_TRY(launch_walk(a, L.n_groups, L.max_slots, L.wide, L.entry_shift, rows, s));
+  return WDF_OK;
+}
+
   const wdf_model *M = bg->model;
-  // the coarsest level whose 64-row blocks fill the device (two per CU); for
-  // fewer rows the finest, and the fewest rows per block that stay within two
-  // blocks per CU
+  // the coarsest level whose 64-row blocks fill the device (two per CU), for
+  // fewer rows the finest
   const int64_t blocks = 2 * (int64_t)M->ctx->n_cu, tiles = (n + 63) / 64;
   const WalkLevel *L = nullptr;
   for (const auto &l : M->walk) {
@@ -328,13 +379,11 @@ int walk_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float
     if (tiles * L->n_groups >= blocks) break;
   }
   if (!L) return set_error(WDF_E_INVALID_ARG, "explain: no walk plan");
-  const WalkArgs a{X, ldx, n, phi, ldphi, bg->d_xtab.as<float>(), L->ops.as<WalkOp>(), L->segs.as<int2>(),
-                   L->groups.as<WalkGroup>(), L->chunks.as<WalkChunk>(), L->runs.as<WalkRun>(),
-                   L->entries.as<WalkEntry>(), M->n_features, 0};
-  int rows = 1;
-  while (rows < 64 && (n + rows - 1) / rows * L->n_groups > blocks) rows *= 4;
-  HIP_TRY(launch_walk(a, L->n_groups, L->max_slots, L->wide, L->entry_shift, rows, s));
-  return WDF_OK;
+  return walk_launch(M, *L, bg->d_xtab.as<float>(), X, n, ldx, phi, ldphi, s);
+}
+
+int walk_explain_iv(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *iv, int64_t ldiv, hipStream_t s) {
+  return walk_launch(bg->model, *bg->model->walk_iv, bg->d_tab.as<float>(), X, n, ldx, iv, ldiv, s);
 }
 
 }  // namespace wdf

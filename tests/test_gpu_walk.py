@@ -70,3 +70,18 @@ def test_generic_histograms_and_phi(loaded):
     assert torch.equal(b.explain(X[:, 11:111]), phi[:, 11:111])
     ref = oracle.bg_walk(oracle.Model(ens), np.ascontiguousarray(Xn[:, :40]), np.ascontiguousarray(Xn[:, :300]))
     assert_phi_close(phi[:, :40].cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("name,rows,many", [("trees", (1, 3, 64, 65, 512, 513, 1025), 8192),   # many: the generated kernels
+                                            ("pool", (1, 5, 64, 130, 512), 4000)])             # many: the generic ones
+def test_few_interaction_rows_equal_many(name, rows, many):
+    from paper_2511_09376_amd import wdf
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    data = synth.DataSpec(127 if name == "trees" else 8, False, 0.05)
+    ens = ENSEMBLES["pool"]() if name == "pool" else synth.make_ensemble(synth.ModelSpec(20, 6, 6, 0.0, 127), data, 5)
+    X = torch.from_numpy(synth.make_matrix(data, many, 9)).cuda()
+    bg = wdf.Background(wdf.Model(wdf.Context(0), ens), X[:, :999].contiguous(), values=wdf.SHAPLEY_IV)
+    ref = bg.explain_iv(X)
+    for n in rows:
+        assert torch.equal(bg.explain_iv(X[:, 7:7 + n]), ref[:, :, 7:7 + n]), f"n={n}"
