@@ -705,6 +705,7 @@ static int enqueue_contract(wdf_model *M, wdf_bg *bg, const uint32_t *hist, cons
   const double *freq_r = freq ? freq + M->hist_size : nullptr;  // right leaves' own frequencies
   HIP_TRY(launch_columns(M->d_groups.as<Group>(), M->d_path.as<PathNode>(), G, hist, freq, freq_r, scale,
                          M->d_hclass_off.as<int64_t>(), H, s));
+  const BaseArgs base_args{M->d_groups.as<Group>(), G, hist, freq, freq_r, hist ? 1.0 / (double)bg->m : 1.0, base};
   if (bg->iv) {  // pair products per class, then pair tables
     int rc;
     if ((rc = enqueue_gemms(M, bg, H, S, s, nullptr))) return rc;
@@ -713,16 +714,14 @@ static int enqueue_contract(wdf_model *M, wdf_bg *bg, const uint32_t *hist, cons
     if (bg->iv_spec)  // interleaved tables of the specialised interaction kernel
       HIP_TRY(launch_ivtab(M->d_iv_units.as<IvUnit>(), (int64_t)M->iv_units.size(), bg->d_tab.as<float>(),
                            bg->d_xtab.as<float>(), s));
-    HIP_TRY(launch_base(M->d_groups.as<Group>(), G, hist, freq, freq_r, hist ? 1.0 / (double)bg->m : 1.0, base, s));
+    HIP_TRY(launch_base(base_args, s));
     return WDF_OK;
   }
   int rc;
   if ((rc = enqueue_gemms(M, bg, H, S, s, nullptr))) return rc;
-  HIP_TRY(launch_expand(M->d_groups.as<Group>(), M->d_path.as<PathNode>(), G, M->d_sclass_off.as<int64_t>(), S,
-                        bg->d_tab.as<float>(), nullptr, s));
-  HIP_TRY(launch_xtab(M->jp.d_xunits.as<XUnit>(), (int64_t)M->jp.xunits.size(), bg->d_tab.as<float>(),
-                      bg->d_xtab.as<float>(), s));
-  HIP_TRY(launch_base(M->d_groups.as<Group>(), G, hist, freq, freq_r, hist ? 1.0 / (double)bg->m : 1.0, base, s));
+  HIP_TRY(launch_tables(M->jp.d_xunits.as<XUnit>(), M->jp.d_unit_g0.as<int64_t>(), (int64_t)M->jp.xunits.size(),
+                        M->d_groups.as<Group>(), M->d_path.as<PathNode>(), M->d_sclass_off.as<int64_t>(), S,
+                        bg->d_tab.as<float>(), bg->d_xtab.as<float>(), base_args, s));
   return WDF_OK;
 }
 

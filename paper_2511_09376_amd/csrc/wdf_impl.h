@@ -73,7 +73,7 @@ struct JitPlan {
   bool thr_in_lds = true;       // thresholds searched in LDS (else in global memory)
   int hist_rounds = 2;          // histogram blocks per CU over the whole launch
   std::vector<int32_t> pad_meta;  // per feature: thr_pad offset, steps (the quantizer's view)
-  DevBuf d_pad_meta, d_perm, d_thr_pad, d_xunits;
+  DevBuf d_pad_meta, d_perm, d_thr_pad, d_xunits, d_unit_g0;
 };
 
 // Per-class contraction shape: paths with dprime distinct features.

@@ -64,10 +64,20 @@ struct GemmBatch {
 // 32x32 output blocks (waves) of one class
 inline int gemm_waves(int R, int ncols) { return ((R + 31) / 32) * ((ncols + 31) / 32); }
 hipError_t launch_gemm_f64(const GemmBatch &batch, int waves, hipStream_t s);
-hipError_t launch_expand(const Group *groups, const PathNode *path, int64_t n_groups, const int64_t *s_class_off,
-                         const double *S, float *tab, double *tab64, hipStream_t s);
-hipError_t launch_base(const Group *groups, int64_t n_groups, const uint32_t *hist, const double *freq,
-                       const double *freq_r, double scale, double *out, hipStream_t s);
+// The base value: hist, or freq and freq_r (path-dependent).
+struct BaseArgs {
+  const Group *groups;
+  int64_t n_groups;
+  const uint32_t *hist;
+  const double *freq, *freq_r;
+  double scale;
+  double *out;
+};
+hipError_t launch_base(const BaseArgs &b, hipStream_t s);
+// gather tables, explain tables and the base value; unit_g0: first group of every unit
+hipError_t launch_tables(const XUnit *units, const int64_t *unit_g0, int64_t n_units, const Group *groups,
+                         const PathNode *path, const int64_t *s_class_off, const double *S, float *tab, float *xtab,
+                         const BaseArgs &base, hipStream_t s);
 hipError_t launch_pd_freq(const Group *groups, int64_t n_groups, const double *ratio, const double *ratio_r,
                           double *freq, double *freq_r, hipStream_t s);
 hipError_t launch_quantize(const float *X, int64_t n, int64_t ldx, int F, const float *thr_pad, const int2 *meta,
@@ -83,7 +93,6 @@ hipError_t launch_explain_iv(const Group *groups, const PathNode *path, int64_t 
                              const int2 *items, const float *tab, const float *X, int64_t n, int64_t ldx, uint8_t *pat,
                              float *out, int64_t ldo, int F, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);
-hipError_t launch_xtab(const XUnit *units, int64_t n_units, const float *tab, float *xtab, hipStream_t s);
 // device address, on the current device, of the library's scratch array
 // (WDF_NOALLOC_SCRATCH_BYTES bytes) used by the entry points that allocate nothing
 hipError_t scratch_address(void **out);

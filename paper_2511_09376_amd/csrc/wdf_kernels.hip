@@ -409,42 +409,13 @@ __global__ __launch_bounds__(256) void k_gemm_f64(const GemmBatch batch) {
   else gemm_wave_small(c, br, bc, lane);
 }
 
-// tab[g][k][p] = S_l[merge(k)][g(p)] + S_r[merge(k)][g(p ^ 1)] at the first
-// position of each feature on the path, 0 at later repeats.
-__global__ __launch_bounds__(256) void k_expand(const Group *__restrict__ groups,
-                                                const PathNode *__restrict__ path,
-                                                const int64_t *__restrict__ s_class_off,
-                                                const double *__restrict__ S, float *__restrict__ tab,
-                                                double *__restrict__ tab64) {
-  const Group g = groups[blockIdx.x];
-  if (g.depth == 0) return;
-  const int d = g.depth, dp = g.dprime;
-  const int64_t K = 1 << dp, R = (int64_t)dp * K;
-  const PathNode *pn = path + g.path_off;
-  const double *Sc = S + s_class_off[dp];
-  const int total = d << d;
-  for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    const int k = idx >> d;
-    const uint32_t p = (uint32_t)(idx & ((1 << d) - 1));
-    double v = 0.0;
-    if (pn[k].first) {
-      const int64_t row = (int64_t)pn[k].merge * K;
-      v = Sc[(int64_t)g.col_l * R + row + merge_pattern(pn, d, dp, p)];
-      if (g.col_r >= 0) v += Sc[(int64_t)g.col_r * R + row + merge_pattern(pn, d, dp, p ^ 1u)];
-    }
-    tab[g.tab_off + idx] = (float)v;
-    if (tab64) tab64[g.tab_off + idx] = v;
-  }
-}
-
 // Base value: sum over groups of w_l * c[all ones] + w_r * c[all ones ^ 1]
 // (path-dependent: w_l * freq[all ones] + w_r * freq_r[all ones]), times
-// scale; one block, fixed reduction order (deterministic).
-__global__ __launch_bounds__(256) void k_base(const Group *__restrict__ groups, int64_t n_groups,
-                                              const uint32_t *__restrict__ hist,
-                                              const double *__restrict__ freq, const double *__restrict__ freq_r,
-                                              double scale, double *__restrict__ out) {
-  __shared__ double part[256];
+// scale; one block of 256, fixed reduction order (deterministic).
+__device__ __forceinline__ void base_value(const Group *__restrict__ groups, int64_t n_groups,
+                                           const uint32_t *__restrict__ hist, const double *__restrict__ freq,
+                                           const double *__restrict__ freq_r, double scale, double *__restrict__ out,
+                                           double *part) {
   double s = 0.0;
   for (int64_t gi = threadIdx.x; gi < n_groups; gi += 256) {
     const Group g = groups[gi];
@@ -463,6 +434,11 @@ __global__ __launch_bounds__(256) void k_base(const Group *__restrict__ groups, 
     __syncthreads();
   }
   if (threadIdx.x == 0) out[0] = part[0] * scale;
+}
+
+__global__ __launch_bounds__(256) void k_base(const BaseArgs b) {
+  __shared__ double part[256];
+  base_value(b.groups, b.n_groups, b.hist, b.freq, b.freq_r, b.scale, b.out, part);
 }
 
 // Section 8: freq[p] = prod over the leaf's path positions of r (bit 1) or
@@ -558,17 +534,8 @@ hipError_t launch_gemm_f64(const GemmBatch &batch, int waves, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_expand(const Group *groups, const PathNode *path, int64_t n_groups, const int64_t *s_class_off,
-                         const double *S, float *tab, double *tab64, hipStream_t s) {
-  if (n_groups <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_expand, dim3((unsigned)n_groups), dim3(256), 0, s, groups, path, s_class_off, S, tab,
-                     tab64);
-  return hipGetLastError();
-}
-
-hipError_t launch_base(const Group *groups, int64_t n_groups, const uint32_t *hist, const double *freq,
-                       const double *freq_r, double scale, double *out, hipStream_t s) {
-  hipLaunchKernelGGL(k_base, dim3(1), dim3(256), 0, s, groups, n_groups, hist, freq, freq_r, scale, out);
+hipError_t launch_base(const BaseArgs &b, hipStream_t s) {
+  hipLaunchKernelGGL(k_base, dim3(1), dim3(256), 0, s, b);
   return hipGetLastError();
 }
 
@@ -918,39 +885,90 @@ hipError_t launch_explain_iv(const Group *groups, const PathNode *path, int64_t 
   return hipGetLastError();
 }
 
-// Explain tables from the gather tables: each unit re-indexed by raw splits
-// and laid out in float4 planes; quads built from their two pair tables.  For a quad of pair depth d, entry I (d+1 bits:
-// prefix, s_a, s_aL, s_aR) has the left pair pattern (prefix, s_a, s_aL) and
-// the right pair pattern (prefix, !s_a, s_aR); value v < d-1 sums both pairs
-// at path position v, v = d-1 is the left pair's last position, v = d the
-// right pair's.
-__global__ __launch_bounds__(256) void k_xtab(const XUnit *__restrict__ units, const float *__restrict__ tab,
-                                              float *__restrict__ xtab) {
+// Gather and explain tables of one unit (a group, or the two pair groups of a
+// quad), and in the last block the base value.
+//
+// Gather tables: tab[g][k][p] = S_l[merge(k)][g(p)] + S_r[merge(k)][g(p ^ 1)]
+// at the first position of each feature on the path, 0 at later repeats.  A
+// thread takes a pattern p and merges it once for all its values (both leaves'
+// 2 d' products of 8 bytes, the positions' features from LDS).
+//
+// Explain tables: the unit re-indexed by raw splits and laid out in float4
+// planes.  For a quad of pair depth d, entry I (d+1 bits: prefix, s_a, s_aL,
+// s_aR) has the left pair pattern (prefix, s_a, s_aL) and the right pair
+// pattern (prefix, !s_a, s_aR); value v < d-1 sums both pairs at path position
+// v, v = d-1 is the left pair's last position, v = d the right pair's.
+//
+// Bound by latency (100 depth-6 trees: 20 MB of products read, 11 MB of tables
+// written, ~7 us at the rate of a large copy).  As three launches (a thread per
+// table entry that merged its pattern from global memory twice, tables read
+// back, the base value in one block of its own) 17.6 + 7.8 + 13.8 us, now 16.6.
+__global__ __launch_bounds__(256) void k_tables(const XUnit *__restrict__ units, const int64_t *__restrict__ unit_g0,
+                                                int64_t n_units, const Group *__restrict__ groups,
+                                                const PathNode *__restrict__ path,
+                                                const int64_t *__restrict__ s_class_off, const double *__restrict__ S,
+                                                float *__restrict__ tab, float *__restrict__ xtab, const BaseArgs base) {
+  __shared__ float t[2][WDF_MAX_DEPTH << WDF_MAX_DEPTH];
+  __shared__ double part[256];
+  if ((int64_t)blockIdx.x == n_units) {
+    base_value(base.groups, base.n_groups, base.hist, base.freq, base.freq_r, base.scale, base.out, part);
+    return;
+  }
   const XUnit u = units[blockIdx.x];
   const int d = u.depth, P = 1 << d;
+  if (d == 0) return;
+  for (int h = 0; h <= u.quad; ++h) {
+    const Group g = groups[unit_g0[blockIdx.x] + h];
+    const int dp = g.dprime;
+    const int64_t K = 1 << dp, R = (int64_t)dp * K;
+    const PathNode *pn = path + g.path_off;
+    const double *Sl = S + s_class_off[dp] + (int64_t)g.col_l * R, *Sr = S + s_class_off[dp] + (int64_t)g.col_r * R;
+    // the 2^d patterns side by side, the positions over the rest of the block
+    const int p = (int)threadIdx.x & (P - 1), k0 = (int)threadIdx.x >> d, kstep = 256 >> d;
+    uint32_t ml = (uint32_t)K - 1u, mr = ml;
+    for (int k = 0; k < d; ++k) {
+      const uint32_t bit = 1u << (dp - 1 - pn[k].merge);
+      if (!((p >> (d - 1 - k)) & 1)) ml &= ~bit;
+      if (!(((p ^ 1) >> (d - 1 - k)) & 1)) mr &= ~bit;
+    }
+    for (int k = k0; k < d; k += kstep) {
+      double v = 0.0;
+      if (pn[k].first) {
+        const int64_t row = (int64_t)pn[k].merge * K;
+        v = Sl[row + ml];
+        if (g.col_r >= 0) v += Sr[row + mr];
+      }
+      t[h][(k << d) + p] = (float)v;
+      tab[g.tab_off + (k << d) + p] = (float)v;
+    }
+  }
+  __syncthreads();
   const int E = 1 << (d + u.quad), planes = (u.nv + 3) / 4;
-  const float *tl = tab + u.src_l, *tr = tab + u.src_r;
-  for (int i = threadIdx.x; i < planes * E * 4; i += blockDim.x) {
-    const int v = (i / (4 * E)) * 4 + (i & 3), I = (i / 4) % E;
-    // entry I sits at slot xunit_slot(I) of its plane (a bijection on [0, E)
-    // that spreads entries over the LDS bank groups)
-    const int slot = (i / (4 * E)) * 4 * E + 4 * xunit_slot(u, I) + (i & 3);
-    float val = 0.f;
-    if (v < u.nv) {
+  const float *tl = t[0], *tr = t[1];
+  for (int i = threadIdx.x; i < planes * E; i += blockDim.x) {
+    const int I = i & (E - 1), v0 = (i >> (d + u.quad)) * 4;
+    float q[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int v = v0 + c;
+      q[c] = 0.f;
+      if (v >= u.nv) continue;
       if (!u.quad) {
-        val = tl[v * P + (I ^ (int)u.mask)];
+        q[c] = tl[v * P + (I ^ (int)u.mask)];
       } else {
         // raw splits: the node and its left child go left on the left pair's
         // path, the node goes right and its right child left on the right pair's
         const int prefix = (I >> 3) ^ (int)u.mask, sa = (I >> 2) & 1, sl = (I >> 1) & 1, sr = I & 1;
         const int pl = (prefix << 2) | (sa << 1) | sl;
         const int pr = (prefix << 2) | ((1 - sa) << 1) | sr;
-        if (v < d - 1) val = tl[v * P + pl] + tr[v * P + pr];
-        else if (v == d - 1) val = tl[(d - 1) * P + pl];
-        else val = tr[(d - 1) * P + pr];
+        if (v < d - 1) q[c] = tl[v * P + pl] + tr[v * P + pr];
+        else if (v == d - 1) q[c] = tl[(d - 1) * P + pl];
+        else q[c] = tr[(d - 1) * P + pr];
       }
     }
-    xtab[u.dst + slot] = val;
+    // entry I sits at slot xunit_slot(I) of its plane (a bijection on [0, E)
+    // that spreads entries over the LDS bank groups)
+    *(float4 *)(xtab + u.dst + (int64_t)v0 * E + 4 * xunit_slot(u, I)) = make_float4(q[0], q[1], q[2], q[3]);
   }
 }
 
@@ -976,9 +994,11 @@ static __device__ __align__(256) uint8_t scratch[WDF_NOALLOC_SCRATCH_BYTES];
 
 hipError_t scratch_address(void **out) { return hipGetSymbolAddress(out, HIP_SYMBOL(scratch)); }
 
-hipError_t launch_xtab(const XUnit *units, int64_t n_units, const float *tab, float *xtab, hipStream_t s) {
-  if (n_units <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_xtab, dim3((unsigned)n_units), dim3(256), 0, s, units, tab, xtab);
+hipError_t launch_tables(const XUnit *units, const int64_t *unit_g0, int64_t n_units, const Group *groups,
+                         const PathNode *path, const int64_t *s_class_off, const double *S, float *tab, float *xtab,
+                         const BaseArgs &base, hipStream_t s) {
+  hipLaunchKernelGGL(k_tables, dim3((unsigned)(n_units + 1)), dim3(256), 0, s, units, unit_g0, n_units, groups, path,
+                     s_class_off, S, tab, xtab, base);
   return hipGetLastError();
 }
 

@@ -222,8 +222,9 @@ static const int kWalkColumns[] = {64, 16, 4};
 int walk_build_explain(wdf_model *M) {
   JitPlan &P = M->jp;
   const int F = M->n_features;
-  int rc = upload(P.d_xunits, P.xunits, M->ctx->stream);
-  if (rc) return rc;
+  int rc;
+  if ((rc = upload(P.d_xunits, P.xunits, M->ctx->stream)) || (rc = upload(P.d_unit_g0, P.unit_g0, M->ctx->stream)))
+    return rc;
   std::vector<WalkUnit> units;
   std::vector<std::vector<ColumnEntry>> cols((size_t)F);
   bool wide = false;
