@@ -1863,10 +1863,26 @@ HistLaunch hist_launch(const wdf_model *M, int64_t m) {
   L.threads = P.nt_hist;
   L.ntiles = (m + 63) / 64;
   const int64_t waves = P.nt_hist / 64;
-  int64_t blocks = std::max<int64_t>(1, (int64_t)P.hist_rounds * M->ctx->n_cu / L.chunks);
-  blocks = std::min<int64_t>(blocks, (L.ntiles + waves - 1) / waves);
-  L.tiles_per_block = (L.ntiles + blocks - 1) / blocks;
-  L.blocks = (L.ntiles + L.tiles_per_block - 1) / L.tiles_per_block;
+  auto plan = [&](int rounds) {
+    int64_t blocks = std::max<int64_t>(1, (int64_t)rounds * M->ctx->n_cu / L.chunks);
+    blocks = std::min<int64_t>(blocks, (L.ntiles + waves - 1) / waves);
+    L.tiles_per_block = (L.ntiles + blocks - 1) / blocks;
+    L.blocks = (L.ntiles + L.tiles_per_block - 1) / L.tiles_per_block;
+    return (L.tiles_per_block + waves - 1) / waves;  // tiles of the busiest wave
+  };
+  // Few tiles per wave: the rounds whose whole tiles, and half a tile's time
+  // for clearing and flushing the LDS bins, cost least (100k rows, 100 depth-6
+  // trees: two rounds of two tiles 120 us, one of three 93 us).
+  // From four tiles on the rounding is small and the choice the tuner's.
+  if (plan(P.hist_rounds) < 4) {
+    int best = P.hist_rounds;
+    int64_t cost = -1;
+    for (int r = P.hist_rounds; r >= 1; --r) {
+      const int64_t c = r * (2 * plan(r) + 1);
+      if (cost < 0 || c < cost) cost = c, best = r;
+    }
+    plan(best);
+  }
   return L;
 }
 
