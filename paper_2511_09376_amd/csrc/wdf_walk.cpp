@@ -269,7 +269,6 @@ int walk_build_explain(wdf_model *M) {
   return WDF_OK;
 }
 
-int walk_build_hist(wdf_model *M) {
 // Interaction values: column (i, j) at i F + j, one group per feature i.  The
 // units are the groups' patterns (the interaction tables are indexed by them).
 int walk_build_iv(wdf_model *M) {
@@ -307,6 +306,7 @@ int walk_build_iv(wdf_model *M) {
   return WDF_OK;
 }
 
+int walk_build_hist(wdf_model *M) {
   const int64_t G = (int64_t)M->groups.size();
   Programs prog(M);
   std::vector<WalkUnit> units((size_t)G);
@@ -356,7 +356,6 @@ int walk_hist(const wdf_model *M, const float *B, int64_t m, int64_t ldb, uint32
   return WDF_OK;
 }
 
-int walk_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, hipStream_t s) {
 // level L's columns for n rows: the fewest rows per block that stay within two
 // blocks per CU, else 64
 static int walk_launch(const wdf_model *M, const WalkLevel &L, const float *tab, const float *X, int64_t n, int64_t ldx,
@@ -370,6 +369,7 @@ static int walk_launch(const wdf_model *M, const WalkLevel &L, const float *tab,
   return WDF_OK;
 }
 
+int walk_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, hipStream_t s) {
   const wdf_model *M = bg->model;
   // the coarsest level whose 64-row blocks fill the device (two per CU), for
   // fewer rows the finest
