@@ -1088,9 +1088,12 @@ extern "C" __global__ __launch_bounds__(NT, 2) void EXPLAIN_NAME(const float* __
   // copies ask for them (paper shape 3.74 -> 3.68 ms, 100 uneven trees 0.637 ->
   // 0.613 ms; with every block prefetching all lines it was slower than none).
   const bool l2_prefetch = by_quarters && 4 * P.xtab_size > kL2PrefetchBytes;
+  const int pf_waves = P.nt_explain / 64;
+  const int pf_lanes = (P.stage_floats * 4 + 128 * 32 * pf_waves - 1) / (128 * 32 * pf_waves);  // lanes that cover a stage
   auto prefetch_l2 = [&](size_t s) {
     if (!l2_prefetch || s >= S.size()) return;
     stage_span(s, t0, n16);
+    if (4 * t0 + (int64_t)pf_lanes * pf_waves * 32 * 128 > 4 * P.xtab_size) return;  // all lines inside the tables
     o << "  KEEP(pf); pf = __builtin_amdgcn_raw_buffer_load_b32(trs, pfoff, " << 4 * t0 << "u, 0);\n";
   };
   if (by_quarters)
@@ -1098,10 +1101,8 @@ extern "C" __global__ __launch_bounds__(NT, 2) void EXPLAIN_NAME(const float* __
       << "  const u32 quarter = __builtin_amdgcn_readfirstlane(threadIdx.x / " << NQ << "u);\n"
       << "  const u32 qbase4 = wbase4 & " << 4 * NQ - 1 << "u;  // the wave's first piece of its quarter, in floats\n";
   if (l2_prefetch) {
-    const int waves = P.nt_explain / 64;
-    const int lanes = (P.stage_floats * 4 + 128 * 32 * waves - 1) / (128 * 32 * waves);
     o << "  u32 pf = 0u;\n"
-      << "  const u32 pfoff = (threadIdx.x & 63u) < " << lanes << "u ? (((threadIdx.x & 63u) * " << waves
+      << "  const u32 pfoff = (threadIdx.x & 63u) < " << pf_lanes << "u ? (((threadIdx.x & 63u) * " << pf_waves
       << "u + (threadIdx.x >> 6)) * 32u + ((blockIdx.x >> 3) & 31u)) * 128u : 0x80000000u;  // past the tables: no access\n";
   }
   o << "  if (live) {\n";

@@ -8,6 +8,7 @@
 #include <functional>
 #include <map>
 #include <memory>
+#include <new>
 #include <vector>
 
 #include "wdf.h"
@@ -140,6 +141,16 @@ struct ColumnGroup {
   std::vector<std::pair<int32_t, const std::vector<ColumnEntry> *>> lists;  // (column - col0, entries in unit order)
 };
 
+// no exception leaves a plan's construction (the callers are C entry points)
+template <class Build>
+int guarded(Build build) {
+  try {
+    return build();
+  } catch (const std::bad_alloc &) {
+    return set_error(WDF_E_OOM, "data-driven kernels: out of host memory");
+  }
+}
+
 constexpr int kZeroRun = 32;  // columns one wave clears at a time
 
 int build_level(const wdf_model *M, const std::vector<WalkUnit> &units, const std::vector<ColumnGroup> &groups,
@@ -220,7 +231,7 @@ int build_level(const wdf_model *M, const std::vector<WalkUnit> &units, const st
 // blocks just fill the device (launch).
 static const int kWalkColumns[] = {64, 16, 4};
 
-int walk_build_explain(wdf_model *M) {
+static int build_explain(wdf_model *M) {
   JitPlan &P = M->jp;
   const int F = M->n_features;
   int rc;
@@ -272,7 +283,7 @@ int walk_build_explain(wdf_model *M) {
 
 // Interaction values: column (i, j) at i F + j, one group per feature i.  The
 // units are the groups' patterns (the interaction tables are indexed by them).
-int walk_build_iv(wdf_model *M) {
+static int build_iv(wdf_model *M) {
   const int F = M->n_features;
   M->walk_iv.reset();
   if (F > 4096) return WDF_OK;  // the runs that clear F x F columns would be most of the plan
@@ -313,7 +324,7 @@ int walk_build_iv(wdf_model *M) {
 // eight, which repeat the paths down to them).
 constexpr int64_t kHistSegmentUnits = 8;
 
-int walk_build_hist(wdf_model *M) {
+static int build_hist(wdf_model *M) {
   const int64_t G = (int64_t)M->groups.size();
   Programs prog(M);
   std::vector<WalkUnit> units((size_t)G);
@@ -350,6 +361,16 @@ int walk_build_hist(wdf_model *M) {
       (rc = upload(W.roots, roots, s)))
     return rc;
   return WDF_OK;
+}
+
+int walk_build_explain(wdf_model *M) {
+  return guarded([&] { return build_explain(M); });
+}
+int walk_build_hist(wdf_model *M) {
+  return guarded([&] { return build_hist(M); });
+}
+int walk_build_iv(wdf_model *M) {
+  return guarded([&] { return build_iv(M); });
 }
 
 int walk_hist(const wdf_model *M, const float *B, int64_t m, int64_t ldb, uint32_t *hist, hipStream_t s) {
