@@ -292,16 +292,20 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // reach outputs that are not stored.  Smaller K (d' <= 3) keeps the plain
 // order k = k0 + q with zeros past K.
 __device__ __forceinline__ void gemm_store(const GemmClass &c, int br, int bc, int lane, const v4d (&acc)[2][2]) {
-  // in tile (x, y), output element (row 4*t + lane/16, column lane%16) sits in acc[x][y][t]
+  // the tiles are computed transposed (columns of S along the MFMA's rows): in
+  // tile (x, y), the product of row lane%16 and column 4*t + lane/16 sits in
+  // acc[x][y][t], so 16 lanes store one 128-byte line of a column (with the
+  // rows along the MFMA's rows a store touched 16 columns, 32 bytes of each:
+  // 21.8 us against 19.0, 100 depth-6 trees)
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
     for (int y = 0; y < 2; ++y) {
-      const int ccol = bc * 32 + 16 * y + (lane & 15);
-      const int rbase = br * 32 + 16 * x + (lane >> 4);
+      const int rr = br * 32 + 16 * x + (lane & 15);
+      const int cbase = bc * 32 + 16 * y + (lane >> 4);
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const int rr = rbase + 4 * t;
+        const int ccol = cbase + 4 * t;
         if (rr < c.R && ccol < c.ncols) c.S[(int64_t)ccol * c.R + rr] = acc[x][y][t];
       }
     }
@@ -327,7 +331,7 @@ __device__ __forceinline__ void gemm_wave_small(const GemmClass &c, int br, int 
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[y], acc[x][y], 0, 0, 0);
+      for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[y], a[x], acc[x][y], 0, 0, 0);
   }
   gemm_store(c, br, bc, lane, acc);
 }
@@ -357,7 +361,7 @@ __device__ __forceinline__ void gemm_mfma16(const GemmFrag &f, v4d (&acc)[2][2])
       for (int y = 0; y < 2; ++y) {
         const double av = (s & 1) ? f.a[x][s >> 1].y : f.a[x][s >> 1].x;
         const double bv = (s & 1) ? f.b[y][s >> 1].y : f.b[y][s >> 1].x;
-        acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[x][y], 0, 0, 0);
+        acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv, av, acc[x][y], 0, 0, 0);
       }
 }
 
