@@ -781,11 +781,11 @@ extern "C" int wdf_background_load(wdf_model *M, const float *B, int64_t m, int6
     ldb = m;
   }
   if ((rc = bg->d_hist.alloc((size_t)std::max<int64_t>(M->hist_size, 1) * sizeof(uint32_t)))) return rc;
-  HIP_TRY(hipMemsetAsync(bg->d_hist.ptr, 0, bg->d_hist.bytes, s));
   if (M->jit) {
     if ((rc = ws_reserve(M->ws_codes, (size_t)M->jp.words * (size_t)m * sizeof(uint32_t)))) return rc;
     if ((rc = jit_hist(M, Bd, m, ldb, bg->d_hist.as<uint32_t>(), M->ws_codes.as<uint32_t>(), s))) return rc;
   } else {
+    HIP_TRY(hipMemsetAsync(bg->d_hist.ptr, 0, bg->d_hist.bytes, s));
     if ((rc = walk_hist(M, Bd, m, ldb, bg->d_hist.as<uint32_t>(), s))) return rc;
   }
   if ((rc = contract(M, bg.get(), bg->d_hist.as<uint32_t>(), nullptr, 1.0 / (double)m, s))) return rc;
@@ -820,10 +820,10 @@ static int enqueue_refresh(wdf_bg *bg, const float *B, int64_t ldb, hipStream_t 
   wdf_model *M = bg->model;
   const int64_t m = bg->m;
   int rc;
-  HIP_TRY(launch_fill_u32(bg->d_hist.as<uint32_t>(), std::max<int64_t>(M->hist_size, 1), 0u, s));
   if (M->jit) {
     if ((rc = jit_hist(M, B, m, ldb, bg->d_hist.as<uint32_t>(), bg->own_codes.as<uint32_t>(), s))) return rc;
   } else {
+    HIP_TRY(launch_fill_u32(bg->d_hist.as<uint32_t>(), std::max<int64_t>(M->hist_size, 1), 0u, s));
     if ((rc = walk_hist(M, B, m, ldb, bg->d_hist.as<uint32_t>(), s))) return rc;
   }
   return enqueue_contract(M, bg, bg->d_hist.as<uint32_t>(), nullptr, 1.0 / (double)m, bg->own_H.as<double>(),
@@ -974,7 +974,7 @@ extern "C" int wdf_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t 
   if (bg->iv) return set_error(WDF_E_INVALID_ARG, "wdf_explain: an interaction summary: use wdf_explain_iv");
   wdf_model *M = bg->model;
   hipStream_t s = pick_stream(M->ctx, hip_stream);
-  if (M->jit && n > kWalkMaxRows) return jit_explain(bg, X, n, ldx, phi, ldphi, s);
+  if (M->jit && (n > kWalkMaxRows || (int)M->jp.explain_stages.size() <= kFewStages)) return jit_explain(bg, X, n, ldx, phi, ldphi, s);
   return walk_explain(bg, X, n, ldx, phi, ldphi, s);
 }
 

@@ -102,7 +102,10 @@ struct WalkHist {
 // 36 / 178, 66 / 178, 114 / 175, 164 / 173.  The generated kernel streams all
 // tables through the LDS of every CU it uses, a fixed time; the gather's time
 // grows with the rows once its blocks fill the device.
+// Models of few stages (80 KB each) keep the generated kernel: 10 depth-4
+// trees, 100 rows, 4.8 us against 6.8.
 constexpr int64_t kWalkMaxRows = 2048;
+constexpr int kFewStages = 4;
 // Interaction values of n rows: the data-driven gather (no pattern pass, one
 // launch) for few rows or little work (rows x table values added per row), then
 // the generic kernels (two launches) up to iv_generic_work, then the generated
@@ -240,7 +243,7 @@ int jit_explain_iv(const wdf_bg *bg, const float *X, int64_t ldx, uint8_t *pat, 
                    hipStream_t s);
 int jit_source(wdf_model *M, bool do_compile, std::string &src);
 int validate_and_layout(const wdf_model_desc *d, wdf_model *M);
-// background histograms; `codes` holds P.words * m words of threshold ranks
+// background histograms (hist is cleared first); `codes` holds P.words * m words of threshold ranks
 int jit_hist(wdf_model *M, const float *B, int64_t m, int64_t ldb, uint32_t *hist, uint32_t *codes, hipStream_t s);
 // grid of the specialised histogram kernel for m background rows
 struct HistLaunch {

@@ -80,8 +80,10 @@ hipError_t launch_tables(const XUnit *units, const int64_t *unit_g0, int64_t n_u
                          const BaseArgs &base, hipStream_t s);
 hipError_t launch_pd_freq(const Group *groups, int64_t n_groups, const double *ratio, const double *ratio_r,
                           double *freq, double *freq_r, hipStream_t s);
+// (also clears hist[0, hist_size))
 hipError_t launch_quantize(const float *X, int64_t n, int64_t ldx, int F, const float *thr_pad, const int2 *meta,
-                           int wide, int words, uint32_t *codes, int64_t ldc, hipStream_t s);
+                           int wide, int words, uint32_t *codes, int64_t ldc, uint32_t *hist, int64_t hist_size,
+                           hipStream_t s);
 hipError_t launch_expand_iv(const Group *groups, const PathNode *path, int64_t n_groups, const int64_t *iv_off,
                             const int64_t *s_class_off, const double *S, float *tab, hipStream_t s);
 hipError_t launch_ivtab(const IvUnit *units, int64_t n_units, const float *tab, float *t2, hipStream_t s);

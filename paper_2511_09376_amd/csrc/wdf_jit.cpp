@@ -1890,7 +1890,7 @@ HistLaunch hist_launch(const wdf_model *M, int64_t m) {
 int jit_hist(wdf_model *M, const float *B, int64_t m, int64_t ldb, uint32_t *hist, uint32_t *codes, hipStream_t s) {
   const JitPlan &P = M->jp;
   hipError_t e = launch_quantize(B, m, ldb, M->n_features, P.d_thr_pad.as<float>(), P.d_pad_meta.as<int2>(), P.wide,
-                                 P.words, codes, m, s);
+                                 P.words, codes, m, hist, M->hist_size, s);
   if (e != hipSuccess) return hip_error(e, "quantize");
   const HistLaunch L = hist_launch(M, m);
   const int chunks = (int)L.chunks;

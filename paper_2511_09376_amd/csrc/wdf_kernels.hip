@@ -661,8 +661,13 @@ __device__ __forceinline__ void quantize_rows4(const float *__restrict__ T, cons
 
 __global__ __launch_bounds__(256) void k_quantize(const float *__restrict__ X, int64_t n, int64_t ldx, int F,
                                                   const float *__restrict__ thr_pad, const int2 *__restrict__ meta,
-                                                  int wide, uint32_t *__restrict__ codes, int64_t ldc, int vec4) {
+                                                  int wide, uint32_t *__restrict__ codes, int64_t ldc, int vec4,
+                                                  uint32_t *__restrict__ hist, int64_t hist_size) {
   __shared__ float st[kQuantLds];
+  // the bins the next kernel counts into, cleared here (one launch less)
+  for (int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < hist_size;
+       i += (int64_t)gridDim.x * gridDim.y * 256)
+    hist[i] = 0u;
   const int w = blockIdx.y;
   const int per = wide ? 2 : 4, bits = wide ? 16 : 8;
   const int f0 = w * per, nf = min(F - f0, per);
@@ -697,11 +702,12 @@ __global__ __launch_bounds__(256) void k_quantize(const float *__restrict__ X, i
 }
 
 hipError_t launch_quantize(const float *X, int64_t n, int64_t ldx, int F, const float *thr_pad, const int2 *meta,
-                           int wide, int words, uint32_t *codes, int64_t ldc, hipStream_t s) {
+                           int wide, int words, uint32_t *codes, int64_t ldc, uint32_t *hist, int64_t hist_size,
+                           hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int vec4 = ldx % 4 == 0 && ldc % 4 == 0 && ((uintptr_t)X & 15u) == 0 && ((uintptr_t)codes & 15u) == 0;
   hipLaunchKernelGGL(k_quantize, dim3((unsigned)((n + kQuantRows - 1) / kQuantRows), (unsigned)words), dim3(256), 0, s,
-                     X, n, ldx, F, thr_pad, meta, wide, codes, ldc, vec4);
+                     X, n, ldx, F, thr_pad, meta, wide, codes, ldc, vec4, hist, hist_size);
   return hipGetLastError();
 }
 

@@ -79,10 +79,8 @@ extern "C" int wdf_model_autotune(wdf_model *M, const float *B, int64_t m, int64
       for (int r : {1, 2, 3, 4, 6, 8}) {
         M->jp.nt_hist = threads[ti];
         M->jp.hist_rounds = r;
-        const float ms = time_runs(s, reps, [&] {
-          HIP_TRY(launch_fill_u32(hist.as<uint32_t>(), std::max<int64_t>(M->hist_size, 1), 0u, s));
-          return jit_hist(M, B, m, ldb, hist.as<uint32_t>(), codes.as<uint32_t>(), s);
-        }, rc);
+        const float ms = time_runs(
+            s, reps, [&] { return jit_hist(M, B, m, ldb, hist.as<uint32_t>(), codes.as<uint32_t>(), s); }, rc);
         if (rc) {
           M->jp.hist_rounds = keep_r;
           M->jp.nt_hist = keep_t;
