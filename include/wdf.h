@@ -210,6 +210,8 @@ int wdf_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float 
  * registers and stores row i of each row's matrix (kernels generated for the
  * model, which stream each feature's tables and the rows' patterns through
  * LDS, or a generic kernel walking i's (group, j) work list sorted by j).
+ * Calls of few rows keep the patterns in LDS (the workspace is checked all the
+ * same); the values' bits do not depend on the kernels.
  * Asynchronous on hip_stream; allocates nothing.
  * Errors: INVALID_ARG (NULL, sizes, small or misaligned workspace, summary
  * not of an interaction kind), UNSUPPORTED (more than 65535 groups), DEVICE. */
@@ -336,7 +338,8 @@ typedef struct {
                                  into quad tables, 0 = pair tables only (WDF_MAX_DEPTH: all) */
   int explain_rows;           /* chosen explain tile: 512 (one block per CU, all of the LDS) or 256
                                  rows per block (two per CU, half of it each) */
-  int hist_rounds;            /* chosen histogram grid: blocks per CU over the launch */
+  int hist_rounds;            /* chosen histogram grid: blocks per CU over the launch (fewer
+                                 where a wave would have less than four tiles) */
   int hist_threads;           /* chosen histogram block: 512, 768 or 1024 threads (at most the
                                  launch bound the model's histogram kernel was compiled for) */
   float explain_ms[WDF_MAX_DEPTH + 1];  /* explain time per quads value, 512-row tiles */
