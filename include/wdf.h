@@ -190,7 +190,10 @@ int wdf_bg_specialised(const wdf_bg *bg);
  * phi[f * ldphi + r] = value of feature f for consumer row r, r < n.  X and phi
  * are device pointers (column-major), n >= 0, ldx >= n, ldphi >= n.  Every
  * feature row of phi in [0, n_features) is written (exact 0.0 for features no
- * path uses).  Asynchronous on `hip_stream`; the caller keeps X and phi alive
+ * path uses).  A model with specialised kernels explains in place as well: phi
+ * may be X itself (the same pointer and stride).  Any other overlap of X and
+ * phi, or one with a generic model, leaves phi undefined.
+ * Asynchronous on `hip_stream`; the caller keeps X and phi alive
  * until the stream reaches this work.  Allocates nothing; read-only on bg, so
  * concurrent calls on different streams are safe.
  * Errors: INVALID_ARG, DEVICE. */
@@ -211,7 +214,8 @@ int wdf_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float 
  * model, which stream each feature's tables and the rows' patterns through
  * LDS, or a generic kernel walking i's (group, j) work list sorted by j).
  * Calls of few rows keep the patterns in LDS (the workspace is checked all the
- * same); the values' bits do not depend on the kernels.
+ * same); the values' bits do not depend on the kernels.  Of calls of up to 32768
+ * rows all of X is read before any of iv is written, so the two may overlap.
  * Asynchronous on hip_stream; allocates nothing.
  * Errors: INVALID_ARG (NULL, sizes, small or misaligned workspace, summary
  * not of an interaction kind), UNSUPPORTED (more than 65535 groups), DEVICE. */
@@ -280,6 +284,14 @@ void wdf_graph_destroy(wdf_graph *g);
  * Errors: INVALID_ARG (NULL, n < 0, ldx < n), DEVICE. */
 int wdf_debug_patterns(const wdf_model *model, const float *X, int64_t n, int64_t ldx, uint32_t *out,
                        void *hip_stream);
+/* The kernels an explain call of n >= 1 rows runs (wdf_explain, or
+ * wdf_explain_iv for an interaction summary): 0 the ones generated for the
+ * model, 1 the data-driven gather, 2 (interaction values) the generic pattern
+ * pass and work lists.  X and out are only compared, to see whether they may
+ * share memory; neither is read.  For tests; needs no device work.
+ * Errors: INVALID_ARG (NULL summary, sizes). */
+int wdf_debug_explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *out,
+                            int64_t ldo);
 /* Time the MFMA contraction of a summary (Section 7 steps (e)-(f)): the
  * FP64 GEMM launches S = M_{d'} H_{d'}, one per distinct-feature class, run
  * `reps` times on hip_stream (after one untimed run) from the summary's

@@ -965,6 +965,48 @@ extern "C" int wdf_base_value(const wdf_bg *bg, double *out) {
 // Explain
 // ---------------------------------------------------------------------------
 
+// Whether [n rows][rows_a columns] at a and [n][rows_b] at b may share memory:
+// their ranges meet, and they are not two column slices of one matrix side by
+// side.
+static bool may_share(const float *a, int64_t lda, int64_t rows_a, const float *b, int64_t ldb, int64_t rows_b,
+                      int64_t n) {
+  const uintptr_t a0 = (uintptr_t)a, a1 = a0 + sizeof(float) * (uintptr_t)((rows_a - 1) * lda + n);
+  const uintptr_t b0 = (uintptr_t)b, b1 = b0 + sizeof(float) * (uintptr_t)((rows_b - 1) * ldb + n);
+  if (a1 <= b0 || b1 <= a0) return false;
+  if (lda == ldb) {
+    const int64_t row = (int64_t)sizeof(float) * lda, width = (int64_t)sizeof(float) * n;
+    const int64_t at = (((int64_t)(b0 - a0)) % row + row) % row;  // b's first column within a's rows
+    if (at >= width && at <= row - width) return false;
+  }
+  return true;
+}
+
+// The kernels a call runs.  A call whose output may be its input's memory
+// keeps to the kernels that read all of a row before they write any of it: the
+// generated explain kernel, and the interaction kernels behind a pattern pass
+// (the gather's blocks of other output columns read the same rows).
+Route wdf::explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *phi, int64_t ldphi) {
+  const wdf_model *M = bg->model;
+  if (!M->jit) return Route::gather;
+  if (n > kWalkMaxRows || (int)M->jp.explain_stages.size() <= kFewStages) return Route::generated;
+  return may_share(X, ldx, M->n_features, phi, ldphi, M->n_features, n) ? Route::generated : Route::gather;
+}
+
+Route wdf::explain_iv_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *iv, int64_t ldiv) {
+  const wdf_model *M = bg->model;
+  const int64_t work = n * M->iv_values, F = M->n_features;
+  if (M->walk_iv && (n <= kWalkIvRows || work <= kWalkIvWork) && !may_share(X, ldx, F, iv, ldiv, F * F, n))
+    return Route::gather;
+  return bg->iv_spec && work > iv_generic_work(M->n_nodes) ? Route::generated : Route::listed;
+}
+
+extern "C" int wdf_debug_explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *out,
+                                       int64_t ldo) {
+  if (!bg) return set_error(WDF_E_INVALID_ARG, "wdf_debug_explain_route: NULL summary");
+  if (n < 1 || ldx < n || ldo < n) return set_error(WDF_E_INVALID_ARG, "wdf_debug_explain_route: need 1 <= n <= ldx, ldo");
+  return (int)(bg->iv ? explain_iv_route(bg, X, n, ldx, out, ldo) : explain_route(bg, X, n, ldx, out, ldo));
+}
+
 extern "C" int wdf_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi,
                            void *hip_stream) {
   if (!bg) return set_error(WDF_E_INVALID_ARG, "wdf_explain: NULL summary");
@@ -972,9 +1014,8 @@ extern "C" int wdf_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t 
   if (n == 0) return WDF_OK;
   if (!X || !phi) return set_error(WDF_E_INVALID_ARG, "wdf_explain: NULL X or phi");
   if (bg->iv) return set_error(WDF_E_INVALID_ARG, "wdf_explain: an interaction summary: use wdf_explain_iv");
-  wdf_model *M = bg->model;
-  hipStream_t s = pick_stream(M->ctx, hip_stream);
-  if (M->jit && (n > kWalkMaxRows || (int)M->jp.explain_stages.size() <= kFewStages)) return jit_explain(bg, X, n, ldx, phi, ldphi, s);
+  hipStream_t s = pick_stream(bg->model->ctx, hip_stream);
+  if (explain_route(bg, X, n, ldx, phi, ldphi) == Route::generated) return jit_explain(bg, X, n, ldx, phi, ldphi, s);
   return walk_explain(bg, X, n, ldx, phi, ldphi, s);
 }
 
@@ -1000,9 +1041,9 @@ extern "C" int wdf_explain_iv(const wdf_bg *bg, const float *X, int64_t n, int64
   if ((uintptr_t)workspace % 16)
     return set_error(WDF_E_INVALID_ARG, "wdf_explain_iv: workspace not 16-byte aligned");
   hipStream_t s = pick_stream(M->ctx, hip_stream);
-  const int64_t work = n * M->iv_values;
-  if (M->walk_iv && (n <= kWalkIvRows || work <= kWalkIvWork)) return walk_explain_iv(bg, X, n, ldx, iv, ldiv, s);
-  if (bg->iv_spec && work > iv_generic_work(M->n_nodes)) return jit_explain_iv(bg, X, ldx, (uint8_t *)workspace, n, iv, ldiv, s);
+  const Route route = explain_iv_route(bg, X, n, ldx, iv, ldiv);
+  if (route == Route::gather) return walk_explain_iv(bg, X, n, ldx, iv, ldiv, s);
+  if (route == Route::generated) return jit_explain_iv(bg, X, ldx, (uint8_t *)workspace, n, iv, ldiv, s);
   HIP_TRY(launch_explain_iv(M->d_groups.as<Group>(), M->d_path.as<PathNode>(), G, M->d_iv_item_off.as<int32_t>(),
                             M->d_iv_items.as<int2>(), bg->d_tab.as<float>(), X, n, ldx, (uint8_t *)workspace, iv, ldiv,
                             M->n_features, s));

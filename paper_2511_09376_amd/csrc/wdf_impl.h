@@ -252,6 +252,11 @@ HistLaunch hist_launch(const wdf_model *M, int64_t m);
 // Grow a workspace buffer to at least `bytes` (contents are not kept).
 int ws_reserve(DevBuf &buf, size_t bytes);
 int jit_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, hipStream_t s);
+// The kernels that serve an explain call: the model's generated ones, the
+// data-driven gather, or (interaction values) the pattern pass and work lists.
+enum class Route { generated = 0, gather = 1, listed = 2 };
+Route explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *phi, int64_t ldphi);
+Route explain_iv_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *iv, int64_t ldiv);
 // the explain-table units of the model, none larger than max_floats as a quad (wdf_jit.cpp)
 void plan_units(wdf_model *M, int64_t max_floats);
 // Data-driven kernels (wdf_walk.cpp): the plan of the explain walk for the

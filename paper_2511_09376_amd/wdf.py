@@ -39,6 +39,11 @@ KERNEL_GENERIC = 1
 KERNEL_SPECIALISED = 2
 KERNEL_PAIRS = 16          # flag: one table per sibling pair in the specialised gather (no quads)
 
+# kernels of an explain call (Background.explain_route)
+ROUTE_GENERATED = 0
+ROUTE_GATHER = 1           # the data-driven gather
+ROUTE_LISTED = 2           # interaction values: pattern pass and work lists
+
 MAX_DEPTH = 8
 SERVE_ONE_PER_LAUNCH = 1
 SERVE_START_PAUSED = 2
@@ -110,7 +115,7 @@ EXPORTS = [
     "wdf_last_error", "wdf_create", "wdf_destroy", "wdf_model_load", "wdf_model_destroy", "wdf_model_groups",
     "wdf_model_specialised", "wdf_bg_specialised", "wdf_background_load", "wdf_pathdep_load", "wdf_bg_destroy", "wdf_explain",
     "wdf_base_value", "wdf_explain_iv", "wdf_explain_iv_workspace", "wdf_explain_iv_noalloc", "wdf_background_refresh", "wdf_graph_create", "wdf_graph_launch", "wdf_graph_destroy",
-    "wdf_debug_patterns", "wdf_debug_histograms", "wdf_debug_tables", "wdf_debug_time_contraction",
+    "wdf_debug_patterns", "wdf_debug_histograms", "wdf_debug_tables", "wdf_debug_time_contraction", "wdf_debug_explain_route",
     "wdf_debug_specialised_source", "wdf_debug_iv_source", "wdf_debug_coef_matrix", "wdf_model_autotune",
     "wdf_model_set_tuning", "wdf_debug_hist_launch", "wdf_server_create",
     "wdf_server_pause", "wdf_server_submit", "wdf_server_wait", "wdf_server_stats", "wdf_server_destroy",
@@ -152,6 +157,7 @@ def lib():
         L.wdf_debug_histograms.argtypes = [P, P, I64]
         L.wdf_debug_histograms.restype = I64
         L.wdf_debug_time_contraction.argtypes = [P, I, P, C.POINTER(C.c_double), C.POINTER(C.c_float)]
+        L.wdf_debug_explain_route.argtypes = [P, P, I64, I64, P, I64]
         L.wdf_debug_tables.argtypes = [P, P, I64]
         L.wdf_debug_tables.restype = I64
         L.wdf_debug_specialised_source.argtypes = [P, I, I, P, I64]
@@ -417,7 +423,9 @@ class Background:
         return v.value
 
     def explain(self, X, out=None, stream=None):
-        """phi [n_features, n] float32 CUDA tensor for consumer rows X [n_features, n]."""
+        """phi [n_features, n] float32 CUDA tensor for consumer rows X [n_features, n].
+        `out` may be X itself when the model is specialised, and overlaps it in
+        no other way."""
         import torch
         F = self.model.n_features
         X = _colmajor_tensor(X, F, "X")
@@ -504,6 +512,14 @@ class Background:
         f, t = C.c_double(), C.c_float()
         _check(lib().wdf_debug_time_contraction(self.h, reps, _stream_handle(stream), C.byref(f), C.byref(t)))
         return float(t.value), float(f.value)
+
+    def explain_route(self, n: int, X=None, out=None) -> int:
+        """Which kernels explain n rows: ROUTE_GENERATED, ROUTE_GATHER or
+        ROUTE_LISTED; X, out: the call's tensors (two separate ones when None)."""
+        ptr, ld = (lambda t: C.c_void_p(t.data_ptr())), (lambda t: t.stride(t.dim() - 2))
+        return int(_check(lib().wdf_debug_explain_route(
+            self.h, None if X is None else ptr(X), n, n if X is None else ld(X),
+            C.c_void_p(1 << 62) if out is None else ptr(out), n if out is None else ld(out))))
 
     def histograms(self) -> np.ndarray:
         n = _check(lib().wdf_debug_histograms(self.h, None, 0))

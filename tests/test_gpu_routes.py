@@ -1,0 +1,81 @@
+"""Which kernels an explain call runs (wdf_debug_explain_route), and the calls
+whose buffers decide it: phi over X, interaction values over X, column slices
+of one matrix."""
+import pytest
+
+from paper_2511_09376_amd import synth
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def wdf():
+    from paper_2511_09376_amd import wdf as w
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return w
+
+
+@pytest.fixture(scope="module")
+def ctx(wdf):
+    return wdf.Context(0)
+
+
+@pytest.fixture(scope="module")
+def trees(wdf, ctx):
+    """30 depth-5 trees of 30 features (6 explain stages), and 6000 rows."""
+    data = synth.DataSpec(30, False, 0.05)
+    ens = synth.make_ensemble(synth.ModelSpec(30, 5, 5, 0.0, 30), data, 5)
+    return wdf.Model(ctx, ens, wdf.KERNEL_SPECIALISED), torch.from_numpy(synth.make_matrix(data, 6000, 9)).cuda()
+
+
+@pytest.mark.parametrize("n", [1, 65, 1000, 2048, 2049, 5000])
+def test_explain_in_place(wdf, trees, n):
+    model, X = trees
+    bg = wdf.Background(model, X[:, :500].contiguous())
+    ref = bg.explain(X[:, 17:17 + n])
+    assert bg.explain_route(n) == (wdf.ROUTE_GATHER if n <= 2048 else wdf.ROUTE_GENERATED)
+    Y = X[:, 17:17 + n].contiguous()
+    assert bg.explain_route(n, Y, Y) == wdf.ROUTE_GENERATED
+    bg.explain(Y, out=Y)
+    assert torch.equal(Y, ref)
+    W = X.clone()
+    Y = W[:, 17:17 + n]                      # a column slice, the rows around it kept
+    bg.explain(Y, out=Y)
+    assert torch.equal(W[:, 17:17 + n], ref)
+    assert torch.equal(W[:, :17].view(torch.int32), X[:, :17].view(torch.int32))
+    assert torch.equal(W[:, 17 + n:].view(torch.int32), X[:, 17 + n:].view(torch.int32))
+
+
+def test_slices_of_one_matrix_share_nothing(wdf, trees):
+    model, X = trees
+    bg = wdf.Background(model, X[:, :500].contiguous())
+    W = X.clone()
+    for a, b, n, shared in ((0, 100, 100, False), (100, 0, 100, False), (5, 104, 100, True), (104, 5, 100, True),
+                            (0, 5900, 100, False), (5900, 0, 100, False)):
+        Y, out = W[:, a:a + n], W[:, b:b + n]
+        assert bg.explain_route(n, Y, out) == (wdf.ROUTE_GENERATED if shared else wdf.ROUTE_GATHER), (a, b)
+    assert bg.explain_route(100, W[:, :100], W[:, :200][:, 50:150]) == wdf.ROUTE_GENERATED
+    ref = bg.explain(X[:, :100])
+    bg.explain(W[:, :100], out=W[:, 100:200])
+    assert torch.equal(W[:, 100:200], ref)
+
+
+@pytest.mark.parametrize("kname", ["specialised", "generic"])
+def test_interaction_values_over_their_rows(wdf, ctx, trees, kname):
+    """X inside the output: every pattern is taken before a value is stored."""
+    model, X = trees
+    if kname == "generic":
+        ens = synth.make_ensemble(synth.ModelSpec(30, 5, 5, 0.0, 30), synth.DataSpec(30, False, 0.05), 5)
+        model = wdf.Model(ctx, ens, wdf.KERNEL_GENERIC)
+    bg = wdf.Background(model, X[:, :500].contiguous(), values=wdf.SHAPLEY_IV)
+    for n in (1, 100, 512, 4000):
+        ref = bg.explain_iv(X[:, :n])
+        out = torch.full((30, 30, n), 7.0, device="cuda")
+        Y = out.view(900, n)[435:465]
+        Y.copy_(X[:, :n])
+        assert bg.explain_route(n, Y, out) != wdf.ROUTE_GATHER
+        bg.explain_iv(Y, out=out)
+        assert torch.equal(out, ref), n
