@@ -519,8 +519,17 @@ hipError_t launch_walk(WalkArgs a, int n_groups, int max_slots, bool wide, int e
   a.x_off = a.F <= kWalkXFeatures ? (int)lds : -1;
   if (a.x_off >= 0) lds += (size_t)a.F * rows * 4;
   const WalkKernel f = kWalkKernels[entry_shift == 2 ? 2 : wide ? 1 : 0][rows == 1 ? 0 : rows == 4 ? 1 : rows == 16 ? 2 : 3];
-  hipLaunchKernelGGL(f, dim3((unsigned)((a.n + rows - 1) / rows), (unsigned)n_groups), dim3(kWalkThreads), lds, s, a);
-  return hipGetLastError();
+  // a launch holds fewer than 2^32 threads per grid dimension: more rows go in several
+  const int64_t n = a.n, most = (int64_t)(0xffffffffu / kWalkThreads) * rows;
+  for (int64_t r0 = 0; r0 < n; r0 += most) {
+    a.n = n - r0 < most ? n - r0 : most;
+    hipLaunchKernelGGL(f, dim3((unsigned)((a.n + rows - 1) / rows), (unsigned)n_groups), dim3(kWalkThreads), lds, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    a.X += most;
+    a.out += most;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_patterns(const Group *groups, const PathNode *path, int64_t n_groups, const float *X,

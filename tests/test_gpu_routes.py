@@ -79,3 +79,22 @@ def test_interaction_values_over_their_rows(wdf, ctx, trees, kname):
         assert bg.explain_route(n, Y, out) != wdf.ROUTE_GATHER
         bg.explain_iv(Y, out=out)
         assert torch.equal(out, ref), n
+
+
+def test_more_rows_than_one_launch_holds(wdf, ctx):
+    """A generic model of one feature: 512 threads per 64 rows pass 2^32 threads
+    at 536 870 848 rows."""
+    n = 536_870_848 + 1000
+    ens = synth.make_ensemble(synth.ModelSpec(1, 2, 2, 0.0, 1), synth.DataSpec(1, False, 0.0), 3)
+    model = wdf.Model(ctx, ens, wdf.KERNEL_GENERIC)
+    row = torch.linspace(-3, 3, 4099, device="cuda")
+    X = row.repeat(n // 4099 + 1)[None, :n]
+    bg = wdf.Background(model, X[:, :300].contiguous())
+    phi = bg.explain(X)
+    assert torch.equal(phi[:, -5000:], bg.explain(X[:, -5000:]))
+    assert torch.equal(phi[:, :4099 * 1000].view(1000, 4099), phi[:, :4099].expand(1000, 4099))
+    iv = wdf.Background(model, X[:, :300].contiguous(), values=wdf.SHAPLEY_IV)
+    assert iv.explain_route(n) == wdf.ROUTE_GATHER            # one feature: no pairs
+    phi.fill_(7.0)
+    iv.explain_iv(X, out=phi[None])
+    assert not phi[:, -5000:].any() and not phi[:, :5000].any() and int(torch.count_nonzero(phi[:, ::4096])) == 0
