@@ -577,6 +577,8 @@ static int iv_layout_host(wdf_model *M, std::vector<int32_t> &ioff, std::vector<
     ioff[(size_t)f + 1] = (int32_t)(items.size() / 2);
   }
   M->iv_values = (int64_t)items.size() / 2;
+  M->iv_longest = 0;
+  for (int f = 0; f < F; ++f) M->iv_longest = std::max<int64_t>(M->iv_longest, ioff[(size_t)f + 1] - ioff[(size_t)f]);
   if (items.empty()) items.assign(2, 0);
   // Units of the interleaved tables (specialised kernel): per feature i,
   // one per group where i has a first occurrence and a partner, in group
@@ -994,10 +996,12 @@ Route wdf::explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ld
 
 Route wdf::explain_iv_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *iv, int64_t ldiv) {
   const wdf_model *M = bg->model;
-  const int64_t work = n * M->iv_values, F = M->n_features;
-  if (M->walk_iv && (n <= kWalkIvRows || work <= kWalkIvWork) && !may_share(X, ldx, F, iv, ldiv, F * F, n))
-    return Route::gather;
-  return bg->iv_spec && work > iv_generic_work(M->n_nodes) ? Route::generated : Route::listed;
+  const int64_t work = n * M->iv_values, F = M->n_features, tiles = F * ((n + 63) / 64), n_cu = M->ctx->n_cu;
+  const WalkLevel *L = M->walk_iv.get();
+  const bool few = L && ((n <= kWalkIvRows && 2 * tiles <= 7 * n_cu) ||
+                         (work <= kWalkIvWork && n * L->max_column <= kWalkIvColumn));
+  if (few && !may_share(X, ldx, F, iv, ldiv, F * F, n)) return Route::gather;
+  return bg->iv_spec && work > iv_listed_work(M->n_nodes, F, M->iv_longest) ? Route::generated : Route::listed;
 }
 
 extern "C" int wdf_debug_explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *out,

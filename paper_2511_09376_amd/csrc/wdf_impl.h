@@ -88,7 +88,7 @@ struct ClassInfo {
 struct WalkLevel {
   int n_groups = 0, max_slots = 1, entry_shift = 4;
   bool wide = false;
-  int64_t n_entries = 0;
+  int64_t max_column = 0;  // entries of the busiest column
   DevBuf ops, segs, groups, chunks, runs, entries;
 };
 // Plan of the data-driven histogram.
@@ -106,17 +106,33 @@ struct WalkHist {
 // trees, 100 rows, 4.8 us against 6.8.
 constexpr int64_t kWalkMaxRows = 2048;
 constexpr int kFewStages = 4;
-// Interaction values of n rows: the data-driven gather (no pattern pass, one
-// launch) for few rows or little work (rows x table values added per row), then
-// the generic kernels (two launches) up to iv_generic_work, then the generated
-// ones (a pattern pass that walks all trees in one thread per row, and a kernel
-// per four features, over four streams).  Measured, us, gather / generic /
-// generated: 20 depth-6 trees of 127 features, 64 rows 19 / 47 / 163, 512 rows
-// 53 / 65 / 160, 1024 rows 78 / 73 / 165, 6144 rows - / 177 / 196, 8192 rows
-// 446 / 235 / 199; 100 trees, 512 rows 133 / 150 / 427, 4096 rows 711 / 399 /
-// 445; 10 depth-4 trees of 8 features, 8192 rows 15 / - / 61.
-constexpr int64_t kWalkIvRows = 512, kWalkIvWork = 16 << 20;
-inline int64_t iv_generic_work(int64_t n_nodes) { return ((int64_t)56 << 20) + 27 * 1024 * n_nodes; }
+// Interaction values of n rows: the data-driven gather (one launch, no pattern
+// pass), the generic kernels (a pattern pass, then one lane per row and
+// feature over the feature's whole list) or the generated ones (a pattern pass
+// that walks all trees in one thread per row, and a kernel per four features,
+// over four streams).  `work` is rows x table values added per row.
+//
+// The gather: its time grows with the work, the F x n / 64 blocks and the
+// entries of the busiest column, which one lane adds in a row.  Measured on 14
+// models, us, gather / listed / generated: 20 depth-6 trees of 127 features, 64
+// rows 18 / 36 / 152, 512 rows 46 / 54 / 158, 1024 rows 75 / 61 / 172; 60
+// depth-6 trees of 200 features, 512 rows 130 / 112 / - (a block limit); 40
+// depth-6 trees of 8 features, 512 rows 62 / 218 / 141; 200 depth-4 trees over 3
+// features (990 entries in a column), 1024 rows 111 / 179 / 131, 2048 rows
+// 136 / 157 / 119.
+constexpr int64_t kWalkIvRows = 512, kWalkIvWork = 16 << 20, kWalkIvColumn = 1 << 20;
+// The lists: fast while the longest is short beside what the generated kernels
+// take for any number of rows (which grows with the nodes and the features);
+// per value the generated kernels add faster.  Largest work of each side's
+// advantage, millions, measured / this line: 20 depth-6 trees of 127 features
+// 135 / 138, 60 of them 313 / 263, 100 of them 430 / 394, 30 of 200 features
+// 183 / 195, 30 of 60 features 144 / 89, 60 depth-5 trees of 30 features
+// 120 / 90, 100 depth-4 trees of 16 features 92 / 75; lists over 1000 of 4 to 16
+// features none / below 16 (40 depth-6 trees of 8 features, 8192 rows 289
+// listed, 160 generated).
+inline int64_t iv_listed_work(int64_t n_nodes, int64_t n_features, int64_t longest) {
+  return 1000 * (30000 + 37 * n_nodes + 500 * n_features - 130 * longest);
+}
 constexpr int kWalkPatternBytes = 32768;  // pattern rows of a chunk in LDS
 
 }  // namespace wdf
@@ -190,6 +206,7 @@ struct wdf_model {
   std::vector<int32_t> iv_unit_off;
   int64_t iv_units_size = 0;   // floats
   int64_t iv_values = 0;       // table values added per row, all columns
+  int64_t iv_longest = 0;      // of them, those of one feature's list (the longest)
   wdf::DevBuf d_iv_units;
   bool iv_coef_ready[2] = {false, false};
   wdf::DevBuf d_coef_iv[2][WDF_MAX_DEPTH + 1];  // [Shapley/Banzhaf][dprime]

@@ -213,7 +213,9 @@ int build_level(const wdf_model *M, const std::vector<WalkUnit> &units, const st
   out.max_slots = std::max(most, 1);
   out.wide = wide;
   out.entry_shift = entry_shift;
-  out.n_entries = (int64_t)entries.size();
+  out.max_column = 0;
+  for (const ColumnGroup &cg : groups)
+    for (const auto &l : cg.lists) out.max_column = std::max(out.max_column, (int64_t)l.second->size());
   hipStream_t s = M->ctx->stream;
   int rc;
   if ((rc = upload(out.ops, prog.ops, s)) || (rc = upload(out.segs, prog.segs, s)) ||

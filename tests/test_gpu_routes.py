@@ -1,8 +1,10 @@
-"""Which kernels an explain call runs (wdf_debug_explain_route), and the calls
-whose buffers decide it: phi over X, interaction values over X, column slices
-of one matrix."""
+"""Which kernels an explain call runs (wdf_debug_explain_route), by its buffers
+(phi over X, interaction values over X, column slices of one matrix) and by the
+model and the rows, and that the values do not depend on it."""
+import numpy as np
 import pytest
 
+import oracle
 from paper_2511_09376_amd import synth
 
 torch = pytest.importorskip("torch")
@@ -98,3 +100,33 @@ def test_more_rows_than_one_launch_holds(wdf, ctx):
     phi.fill_(7.0)
     iv.explain_iv(X, out=phi[None])
     assert not phi[:, -5000:].any() and not phi[:, :5000].any() and int(torch.count_nonzero(phi[:, ::4096])) == 0
+
+
+def _model(trees, depth, F, pool=0):
+    data = synth.DataSpec(F, F > 100, 0.05)
+    return synth.make_ensemble(synth.ModelSpec(trees, depth, depth, 0.0, F, **({"feature_pool": pool} if pool else {})), data, 11), data
+
+
+# 0 generated, 1 gather, 2 pattern pass and lists
+@pytest.mark.parametrize("spec,routes", [
+    ((200, 4, 8, 3), {512: 1, 1024: 1, 2048: 0, 9000: 0}),       # 990 entries in a column, lists of 2000
+    ((40, 6, 8), {512: 1, 800: 1, 1024: 0}),                     # lists of 2700
+    ((20, 6, 127), {1: 1, 600: 1, 1024: 2, 7000: 2, 8192: 0}),
+], ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else "")
+def test_interaction_routes(wdf, ctx, spec, routes):
+    ens, data = _model(*spec)
+    F, most = spec[2], max(routes)
+    X = torch.from_numpy(synth.make_matrix(data, most + 9, 4)).cuda()
+    bg, gen = (wdf.Background(wdf.Model(ctx, ens, k), X[:, :999].contiguous(), values=wdf.SHAPLEY_IV)
+               for k in (wdf.KERNEL_SPECIALISED, wdf.KERNEL_GENERIC))
+    assert bg.specialised and not gen.specialised
+    assert gen.explain_route(most) == wdf.ROUTE_LISTED
+    ref = gen.explain_iv(X)
+    for n, route in routes.items():
+        assert bg.explain_route(n) == route, n
+        assert torch.equal(bg.explain_iv(X[:, 7:7 + n]), ref[:, :, 7:7 + n]), n
+    rows = [0, most // 3, most + 8]
+    exact = oracle.bg_iv_walk(oracle.Model(ens), np.ascontiguousarray(X[:, rows].cpu().numpy()),
+                              np.ascontiguousarray(X[:, :999].cpu().numpy()), threads=8)
+    err = np.abs(ref[:, :, rows].cpu().numpy() - exact).max(axis=(0, 1)) / np.abs(exact).max(axis=(0, 1))
+    assert err.max() <= 1e-5
