@@ -1,0 +1,80 @@
+"""The generated interaction kernels against the oracle and the data-driven
+gather, at row counts that reach them (wdf_debug_explain_route): 16-bit ranks,
+root leaves, stumps, repeated features and a depth-8 chain, several chunks of
+rows, and the scratch-backed entry point."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2511_09376_amd import synth
+from tests.test_gpu_parity import _edge_ensemble
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def wdf():
+    from paper_2511_09376_amd import wdf as w
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return w
+
+
+@pytest.fixture(scope="module")
+def ctx(wdf):
+    return wdf.Context(0)
+
+
+def _pool():
+    return synth.make_ensemble(synth.ModelSpec(200, 4, 4, 0.0, 8, feature_pool=3), synth.DataSpec(8, False, 0.0), 11)
+
+
+@pytest.mark.parametrize("kind", ["shapley", "banzhaf"])
+@pytest.mark.parametrize("make,n", [(_edge_ensemble, 600_011), (_pool, 33_003)], ids=["edge", "pool"])
+def test_generated_interaction_kernels(wdf, ctx, make, n, kind):
+    ens = make()
+    F = ens.n_features
+    if make is _pool:
+        assert "WORD_1" in wdf.iv_source(ens)                  # more than 127 thresholds: 16-bit ranks
+    rng = np.random.default_rng(n)
+    X = rng.normal(size=(F, n)).astype(np.float32)
+    X[rng.random(X.shape) < 0.1] = np.nan
+    inner = ens.feature >= 0
+    for c, v in enumerate((ens.threshold[inner], -np.inf, np.inf, np.nan, 0.0, -0.0)):
+        X[ens.feature[inner], c] = v
+    B = rng.normal(size=(F, 33)).astype(np.float32)
+    B[rng.random(B.shape) < 0.1] = np.nan
+    Xd = torch.from_numpy(X).cuda()
+    bg = wdf.Background(wdf.Model(ctx, ens, wdf.KERNEL_SPECIALISED), torch.from_numpy(B).cuda(),
+                        values=wdf.SHAPLEY_IV if kind == "shapley" else wdf.BANZHAF_IV)
+    assert bg.explain_route(n) == wdf.ROUTE_GENERATED and bg.explain_route(300) == wdf.ROUTE_GATHER
+    got = bg.explain_iv(Xd)
+    for a in (0, 32_768 - 150, n - 300):                       # chunks of 32768 rows meet; the ragged end
+        assert torch.equal(bg.explain_iv(Xd[:, a:a + 300].contiguous()), got[:, :, a:a + 300]), a
+    rows = np.r_[0:8, 255:258, 32_766:32_770, n - 3:n]
+    ref = oracle.bg_iv_walk(oracle.Model(ens), np.ascontiguousarray(X[:, rows]), B,
+                            oracle.SHAPLEY if kind == "shapley" else oracle.BANZHAF, threads=8)
+    g = got[:, :, torch.from_numpy(rows).cuda()].cpu().numpy().reshape(F * F, -1).astype(np.float64)
+    r = ref.reshape(F * F, -1)
+    assert (np.abs(g - r).max(0) / np.maximum(np.abs(r).max(0), 1e-30)).max() <= 1e-5
+
+
+def test_generated_kernels_through_the_scratch_array(wdf, ctx):
+    """wdf_explain_iv_noalloc with patterns that the generated kernels write and
+    read, the second call over the first one's."""
+    w = synth.WORKLOADS["small"]
+    ens = w.ensemble()
+    model = wdf.Model(ctx, ens, wdf.KERNEL_SPECIALISED)
+    bg = wdf.Background(model, torch.from_numpy(w.background()).cuda(), values=wdf.SHAPLEY_IV)
+    F = ens.n_features
+    assert bg.iv_workspace_bytes(200_000) <= wdf.NOALLOC_SCRATCH_BYTES
+    X = torch.from_numpy(w.consumers(300_000)).cuda()
+    for a, n in ((0, 200_000), (200_000, 90_001)):
+        assert bg.explain_route(n) == wdf.ROUTE_GENERATED
+        Xn = X[:, a:a + n].contiguous()
+        out = torch.full((F, F, n), float("nan"), device="cuda")
+        bg.explain_iv_noalloc(Xn, out)
+        assert torch.equal(out, bg.explain_iv(Xn))
+        assert torch.equal(out[:, :, -500:], bg.explain_iv(Xn[:, -500:].contiguous()))
