@@ -1,0 +1,73 @@
+"""The data-driven gather bit for bit against the generated explain kernel and
+against the oracle, on models that take it (asserted): irregular trees (root
+leaf, stump, repeats, single leaves, a depth-8 chain, 16-bit slots) and columns
+whose units span several chunks."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2511_09376_amd import synth
+from tests.gpu_util import assert_phi_close
+from tests.test_gpu_parity import _edge_ensemble
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def wdf():
+    from paper_2511_09376_amd import wdf as w
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return w
+
+
+@pytest.fixture(scope="module")
+def ctx(wdf):
+    return wdf.Context(0)
+
+
+def _irregular():
+    a = _edge_ensemble()
+    b = synth.make_ensemble(synth.ModelSpec(60, 1, 8, 0.2, 40), synth.DataSpec(40, False, 0.05), 21)
+    cat = {f.name: np.concatenate([getattr(a, f.name), getattr(b, f.name)]) for f in dataclasses.fields(a)
+           if f.name not in ("n_features", "node_offset")}
+    return dataclasses.replace(b, node_offset=np.r_[a.node_offset, b.node_offset[1:] + a.node_offset[-1]], **cat)
+
+
+def _chunks():   # 1600 units, of which a block of 4 columns needs nearly all: 512 at a time
+    return synth.make_ensemble(synth.ModelSpec(100, 6, 6, 0.0, 8), synth.DataSpec(8, False, 0.05), 11)
+
+
+def _rows(ens, n):
+    rng = np.random.default_rng(7)
+    X = rng.normal(size=(ens.n_features, n)).astype(np.float32)
+    X[rng.random(X.shape) < 0.05] = np.nan
+    inner = ens.feature >= 0
+    for c, v in enumerate((ens.threshold[inner], -np.inf, np.inf, np.nan, 0.0, -0.0)):
+        X[ens.feature[inner], c] = v
+    return X
+
+
+@pytest.mark.parametrize("make", [_irregular, _chunks])
+@pytest.mark.parametrize("pairs", [False, True], ids=["quads", "pairs"])
+def test_gather_equals_the_generated_kernel(wdf, ctx, make, pairs):
+    ens = make()
+    Xn = _rows(ens, 3000)
+    X = torch.from_numpy(Xn).cuda()
+    model = wdf.Model(ctx, ens, wdf.KERNEL_SPECIALISED | (wdf.KERNEL_PAIRS if pairs else 0))
+    for kind in (wdf.SHAPLEY, wdf.BANZHAF):
+        bg = wdf.Background(model, X[:, :777].contiguous(), values=kind)
+        assert bg.explain_route(3000) == wdf.ROUTE_GENERATED
+        ref = bg.explain(X)
+        for n in (1, 2, 5, 17, 63, 64, 65, 513, 1025, 2048):
+            assert bg.explain_route(n) == wdf.ROUTE_GATHER
+            for a in (0, 3):
+                assert torch.equal(bg.explain(X[:, a:a + n]), ref[:, a:a + n]), f"n={n} from {a}"
+    bg = wdf.Background(model, X[:, :300].contiguous())
+    got = bg.explain(X[:, :24].contiguous()).cpu().numpy()
+    assert_phi_close(got, oracle.bg_walk(oracle.Model(ens), np.ascontiguousarray(Xn[:, :24]),
+                                         np.ascontiguousarray(Xn[:, :300]), threads=8))
