@@ -103,9 +103,18 @@ struct WalkHist {
 // tables through the LDS of every CU it uses, a fixed time; the gather's time
 // grows with the rows once its blocks fill the device.
 // Models of few stages (80 KB each) keep the generated kernel: 10 depth-4
-// trees, 100 rows, 4.8 us against 6.8.
+// trees, 100 rows, 4.5 us against 6.8.  So do models one of whose features
+// takes a value from more than half of the units (few features), while their
+// tables stay in an XCD's L2: the gather then computes nearly every slot in
+// each block and adds a column's values one after the other.  Measured, gather
+// from 1 to 2048 rows / generated, us: 200 depth-4 trees over 3 features
+// (0.8 MB) 50-57 / 36, 400 depth-4 trees of 4 (1.6 MB) 89-125 / 72, 40 depth-6
+// trees of 8 (2.6 MB) 43-61 / 38; past the L2 60 depth-6 trees of 12 features
+// (3.9 MB) 47-61 / 67, 300 depth-5 trees of 8 (4.9 MB) 110-162 / 154, 10 depth-8
+// trees of 8 (16 MB) 111-154 / 205.
 constexpr int64_t kWalkMaxRows = 2048;
 constexpr int kFewStages = 4;
+constexpr int64_t kBusyColumnTables = 3 << 20;
 // Interaction values of n rows: the data-driven gather (one launch, no pattern
 // pass), the generic kernels (a pattern pass, then one lane per row and
 // feature over the feature's whole list) or the generated ones (a pattern pass

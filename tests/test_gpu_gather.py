@@ -1,7 +1,7 @@
 """The data-driven gather bit for bit against the generated explain kernel and
 against the oracle, on models that take it (asserted): irregular trees (root
 leaf, stump, repeats, single leaves, a depth-8 chain, 16-bit slots) and columns
-whose units span several chunks."""
+whose units span several chunks.  Few-feature models keep the generated kernel."""
 import dataclasses
 
 import numpy as np
@@ -71,3 +71,18 @@ def test_gather_equals_the_generated_kernel(wdf, ctx, make, pairs):
     got = bg.explain(X[:, :24].contiguous()).cpu().numpy()
     assert_phi_close(got, oracle.bg_walk(oracle.Model(ens), np.ascontiguousarray(Xn[:, :24]),
                                          np.ascontiguousarray(Xn[:, :300]), threads=8))
+
+
+@pytest.mark.parametrize("spec", [(200, 4, 8, 3), (400, 4, 4, 4), (40, 6, 8, 8)])
+def test_few_features_keep_the_generated_kernel(wdf, ctx, spec):
+    """One feature takes a value from more than half of the units, and the
+    tables fit the L2."""
+    trees, depth, F, pool = spec
+    ens = synth.make_ensemble(synth.ModelSpec(trees, depth, depth, 0.0, F, feature_pool=pool),
+                              synth.DataSpec(F, False, 0.05), 11)
+    X = torch.from_numpy(_rows(ens, 600)).cuda()
+    model, generic = wdf.Model(ctx, ens, wdf.KERNEL_SPECIALISED), wdf.Model(ctx, ens, wdf.KERNEL_GENERIC)
+    a, b = wdf.Background(model, X[:, :99].contiguous()), wdf.Background(generic, X[:, :99].contiguous())
+    for n in (1, 64, 600):
+        assert a.explain_route(n) == wdf.ROUTE_GENERATED and b.explain_route(n) == wdf.ROUTE_GATHER
+        torch.testing.assert_close(a.explain(X[:, :n]), b.explain(X[:, :n]), rtol=0, atol=1e-5 * float(b.explain(X).abs().max()))
