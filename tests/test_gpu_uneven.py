@@ -111,6 +111,25 @@ def test_uneven_subset_parity(wdf, uneven, kname):
     print(f"uneven {kname}: row-scaled error {err:.3e}")
 
 
+def test_uneven_rows_spread_over_blocks(wdf, uneven):
+    """More than 256 stages, copied at once, and blocks with waves that hold no
+    rows (5000 rows: 64 a block; 20 011: 128): the rows of a call whose blocks
+    are full, bit for bit, and the oracle's values."""
+    w, ens, ctx, model, X, B = uneven
+    Bs = np.ascontiguousarray(B[:, :4099])
+    bg = wdf.Background(model, torch.from_numpy(Bs).cuda())
+    Xd = torch.from_numpy(np.ascontiguousarray(X[:, :140_000])).cuda()
+    full = bg.explain(Xd)
+    for a, n in ((11, 5000), (100_003, 20_011)):
+        assert bg.explain_route(n) == wdf.ROUTE_GENERATED
+        got = bg.explain(Xd[:, a:a + n])
+        assert torch.equal(got, full[:, a:a + n]), n
+        rows = np.r_[0, 63, 64, n // 2, n - 1]
+        ref = oracle.bg_walk(oracle.Model(ens), np.ascontiguousarray(X[:, a + rows]), Bs, threads=16)
+        assert_phi_close(got[:, torch.from_numpy(rows).cuda()].cpu().numpy(), ref)
+    bg.close()
+
+
 def test_uneven_tile_loop_512(wdf, uneven):
     """Paths of up to eight positions compile the histogram kernel for
     512-thread blocks.  Its tile loop at 60 013 background rows (a ragged last
