@@ -42,8 +42,6 @@ struct Group {
 // chosen per unit so that the entries rows are likely to read together fall
 // in different groups of LDS banks.
 struct XUnit {
-  int64_t src_l;   // table offset of the (left) group
-  int64_t src_r;   // table offset of the right pair group of a quad, -1 otherwise
   int64_t dst;     // offset in the explain tables (floats, multiple of 4)
   int32_t depth;   // depth of the group(s)
   int32_t quad;    // 1 for a quad

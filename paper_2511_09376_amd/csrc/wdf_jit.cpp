@@ -134,15 +134,12 @@ void plan_units(wdf_model *M, int64_t max_floats) {
       }
     }
     XUnit u{};
-    u.src_l = ga.tab_off;
-    u.src_r = quad ? M->groups[(size_t)g + 1].tab_off : -1;
     u.dst = xoff;
     u.depth = ga.depth;
     u.quad = quad ? 1 : 0;
     u.nv = ga.depth + u.quad;
     if (quad && xunit_floats(u) > max_floats) {
       quad = false;
-      u.src_r = -1;
       u.quad = 0;
       u.nv = ga.depth;
     }

@@ -808,15 +808,6 @@ __global__ __launch_bounds__(256) void k_patterns_u8(const Group *__restrict__ g
   pat[gi * n + r] = (uint8_t)group_pattern(groups[gi], path, X, ldx, r);
 }
 
-hipError_t launch_patterns_u8(const Group *groups, const PathNode *path, int64_t n_groups, const float *X, int64_t n,
-                              int64_t ldx, uint8_t *pat, hipStream_t s) {
-  if (n <= 0 || n_groups <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_patterns_u8, dim3((unsigned)((n + 255) / 256), (unsigned)n_groups), dim3(256), 0, s, groups,
-                     path, X, n, ldx, pat);
-  return hipGetLastError();
-}
-
-
 // Interaction values of consumer rows: one wave = 64 rows and one feature i
 // (blockIdx.y).  The wave walks the work list of i: items (offset of the pair
 // table of (i, j) for one group, group << 16 | j), sorted by j, a multiple of
