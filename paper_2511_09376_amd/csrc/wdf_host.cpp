@@ -472,7 +472,7 @@ extern "C" int wdf_model_load(wdf_ctx *ctx, const wdf_model_desc *desc, int kern
   }
   if (!M->jit) {
     try {
-      plan_units(M.get(), INT64_MAX);
+      plan_units(M.get(), INT64_MAX, false);
       if ((rc = walk_build_explain(M.get())) || (rc = walk_build_hist(M.get()))) return rc;
     } catch (const std::bad_alloc &) {
       return set_error(WDF_E_OOM, "wdf_model_load: out of host memory");
@@ -721,7 +721,7 @@ static int enqueue_contract(wdf_model *M, wdf_bg *bg, const uint32_t *hist, cons
   }
   int rc;
   if ((rc = enqueue_gemms(M, bg, H, S, s, nullptr))) return rc;
-  HIP_TRY(launch_tables(M->jp.d_xunits.as<XUnit>(), M->jp.d_unit_g0.as<int64_t>(), (int64_t)M->jp.xunits.size(),
+  HIP_TRY(launch_tables(M->jp.d_xunits, M->jp.d_unit_g0, (int64_t)M->jp.xunits.size(),
                         M->d_groups.as<Group>(), M->d_path.as<PathNode>(), M->d_sclass_off.as<int64_t>(), S,
                         bg->d_tab.as<float>(), bg->d_xtab.as<float>(), base_args, s));
   return WDF_OK;

@@ -73,7 +73,9 @@ struct JitPlan {
   bool thr_in_lds = true;       // thresholds searched in LDS (else in global memory)
   int hist_rounds = 2;          // histogram blocks per CU over the whole launch
   std::vector<int32_t> pad_meta;  // per feature: thr_pad offset, steps (the quantizer's view)
-  DevBuf d_pad_meta, d_perm, d_thr_pad, d_xunits, d_unit_g0;
+  DevBuf d_pad_meta, d_perm, d_thr_pad, d_units;
+  const XUnit *d_xunits = nullptr;     // in d_units
+  const int64_t *d_unit_g0 = nullptr;
 };
 
 // Per-class contraction shape: paths with dprime distinct features.
@@ -89,12 +91,22 @@ struct WalkLevel {
   int n_groups = 0, max_slots = 1, entry_shift = 4;
   bool wide = false;
   int64_t max_column = 0;  // entries of the busiest column
-  DevBuf ops, segs, groups, chunks, runs, entries;
+  DevBuf buf;              // the arrays below
+  const WalkOp *ops = nullptr;
+  const int2 *segs = nullptr;
+  const WalkGroup *groups = nullptr;
+  const WalkChunk *chunks = nullptr;
+  const WalkRun *runs = nullptr;
+  const WalkEntry *entries = nullptr;
 };
 // Plan of the data-driven histogram.
 struct WalkHist {
   int n_chunks = 0, n_roots = 0;
-  DevBuf ops, segs, chunks, roots;
+  DevBuf buf;  // the arrays below
+  const WalkOp *ops = nullptr;
+  const int2 *segs = nullptr;
+  const WalkHistChunk *chunks = nullptr;
+  const int64_t *roots = nullptr;
 };
 // Rows up to which a specialised model explains through the data-driven gather
 // (100 depth-6 trees, us): 1 row 20 against 135 of the generated kernel, 1000
@@ -283,8 +295,9 @@ int jit_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float 
 enum class Route { generated = 0, gather = 1, listed = 2 };
 Route explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *phi, int64_t ldphi);
 Route explain_iv_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *iv, int64_t ldiv);
-// the explain-table units of the model, none larger than max_floats as a quad (wdf_jit.cpp)
-void plan_units(wdf_model *M, int64_t max_floats);
+// the explain-table units of the model, none larger than max_floats as a quad,
+// with or without a fold for the LDS banks (wdf_jit.cpp)
+void plan_units(wdf_model *M, int64_t max_floats, bool folds);
 // Data-driven kernels (wdf_walk.cpp): the plan of the explain walk for the
 // planned units (which it uploads), and of the histogram
 int walk_build_explain(wdf_model *M);

@@ -115,7 +115,7 @@ void choose_fold(const wdf_model *M, XUnit &u, int64_t tree, const std::vector<i
 
 }  // namespace
 
-void plan_units(wdf_model *M, int64_t max_floats) {
+void plan_units(wdf_model *M, int64_t max_floats, bool folds) {
   JitPlan &P = M->jp;
   const int64_t G = (int64_t)M->groups.size();
   // explain-table units: a pair group and the next pair group form a quad
@@ -146,7 +146,7 @@ void plan_units(wdf_model *M, int64_t max_floats) {
     u.mask = 0;
     for (int k = 0; k < (quad ? ga.depth - 2 : ga.depth); ++k)
       u.mask = (u.mask << 1) | M->path[(size_t)ga.path_off + (size_t)k].dir;
-    {
+    if (folds) {
       // the nodes of the index bits: the group's path (and for a quad the
       // right pair's node last)
       std::vector<int64_t> nodes;
@@ -297,7 +297,7 @@ int make_plan(wdf_model *M) {
   if (P.stage_floats < max_table)
     return set_error(WDF_E_UNSUPPORTED, "specialised kernels: %zu thresholds leave too little LDS for the tables",
                      P.thr_pad.size());
-  plan_units(M, P.stage_floats);
+  plan_units(M, P.stage_floats, true);
   // explain stages: consecutive units whose tables fit one LDS buffer (stored
   // as group ranges; a stage never splits a quad)
   P.explain_stages.clear();

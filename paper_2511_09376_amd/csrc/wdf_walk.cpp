@@ -3,9 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <array>
 #include <cstring>
-#include <functional>
 #include <map>
 #include <memory>
 #include <new>
@@ -34,86 +32,91 @@ struct WalkUnit {
 
 // Writes the segments (one per tree, of at most `most` units) of the units
 // [a, b) of `list`, which are in tree and depth-first order; unit list[k] hands
-// its slot to out(k).
+// its slot to out(k).  In that order a unit's path leaves the path of the one
+// before it at some node and its last node is new, so the tests still to do are
+// the path's from there on.
 class Programs {
  public:
-  explicit Programs(const wdf_model *M) : M_(M), mark_((size_t)M->n_nodes, -1), at_((size_t)M->n_nodes, -1) {}
+  explicit Programs(const wdf_model *M) : M_(M) {}
 
   std::vector<WalkOp> ops;
   std::vector<int2> segs;
 
-  void add(const std::vector<WalkUnit> &units, const int32_t *list, int64_t a, int64_t b,
-           const std::function<uint32_t(int64_t)> &out, int64_t most = INT64_MAX) {
+  template <class Out>
+  void add(const std::vector<WalkUnit> &units, const int32_t *list, int64_t a, int64_t b, Out out,
+           int64_t most = INT64_MAX) {
     for (int64_t k = a; k < b;) {
       const int tree = units[(size_t)list[k]].tree;
-      int64_t e = k;
-      while (e < b && e - k < most && units[(size_t)list[e]].tree == tree) ++e;
-      ++stamp_;
-      for (int64_t q = k; q < e; ++q) {
-        const WalkUnit &u = units[(size_t)list[q]];
-        const Group &g = M_->groups[(size_t)u.group];
-        for (int i = 0; i < u.levels; ++i) mark_[(size_t)M_->path_nodes[(size_t)g.path_off + (size_t)i]] = stamp_;
-        at_[(size_t)u.node] = q;
+      const size_t op0 = ops.size();
+      const int64_t base = M_->node_offset[(size_t)tree], stop = b - k < most ? b : k + most;
+      int64_t on[WDF_MAX_DEPTH + 2];  // the nodes whose splits are in P
+      int have = 0;                   // splits in P
+      for (; k < stop && units[(size_t)list[k]].tree == tree; ++k) {
+        const WalkUnit &u = units[(size_t)list[k]];
+        const int64_t *path = &M_->path_nodes[(size_t)M_->groups[(size_t)u.group].path_off];
+        int at = 0;
+        while (at < have && at < u.levels && on[at] == path[at]) ++at;
+        for (; at < u.levels; ++at) {
+          test(path[at], have - at);
+          on[at] = path[at];
+          have = at + 1;
+        }
+        if (u.quad) {  // the two pair nodes below; no other unit's path holds them
+          test(base + M_->left[(size_t)u.node], 0);
+          test(base + M_->right[(size_t)u.node], 0);
+          on[have] = on[have + 1] = -1;
+          have += 2;
+        }
+        WalkOp &o = ops.back();
+        o.ctl |= kWalkEmit | (uint32_t)(u.fold_a ? u.fold_a : 31) << 8 | (uint32_t)(u.fold_b ? u.fold_b : 31) << 16;
+        o.out = out(k) | u.mask << 20;
       }
-      const int64_t op0 = (int64_t)ops.size();
-      base_ = M_->node_offset[(size_t)tree];
-      have_ = 0;
-      visit(base_, 0, units, list, out);
-      for (int64_t q = k; q < e; ++q) at_[(size_t)units[(size_t)list[q]].node] = -1;
-      while ((ops.size() - (size_t)op0) % 4) ops.push_back(WalkOp{0, 0u, 31u << 8 | 31u << 16, 0u});
+      while ((ops.size() - op0) % 4) ops.push_back(WalkOp{0, 0u, 31u << 8 | 31u << 16, 0u});
       segs.push_back(int2{(int)op0, (int)ops.size()});
-      k = e;
     }
   }
 
  private:
-  // test of `node` with `depth` path nodes above it
-  void test(int64_t node, int depth) {
+  void test(int64_t node, int drop) {
     const uint32_t bias = M_->default_left[(size_t)node] ? 0u : 1u;
     uint32_t b;
     std::memcpy(&b, &M_->threshold[(size_t)node], sizeof b);
-    ops.push_back(WalkOp{M_->feature[(size_t)node], walk_key_bits(b) - bias,
-                         (uint32_t)(have_ - depth) | (bias ? kWalkBias : 0u), 0u});
-    have_ = depth + 1;
-  }
-  void emit(const WalkUnit &u, uint32_t out) {
-    WalkOp &o = ops.back();
-    o.ctl |= kWalkEmit | (uint32_t)(u.fold_a ? u.fold_a : 31) << 8 | (uint32_t)(u.fold_b ? u.fold_b : 31) << 16;
-    o.out = out | u.mask << 20;
-  }
-  void visit(int64_t node, int depth, const std::vector<WalkUnit> &units, const int32_t *list,
-             const std::function<uint32_t(int64_t)> &out) {
-    if (mark_[(size_t)node] != stamp_) return;
-    test(node, depth);
-    const int64_t L = base_ + M_->left[(size_t)node], R = base_ + M_->right[(size_t)node];
-    const int64_t k = at_[(size_t)node];
-    if (k >= 0) {
-      const WalkUnit &u = units[(size_t)list[k]];
-      if (u.quad) {
-        test(L, depth + 1);
-        test(R, depth + 2);
-      }
-      emit(u, out(k));
-      if (u.quad) return;
-    }
-    if (M_->feature[(size_t)L] >= 0) visit(L, depth + 1, units, list, out);
-    if (M_->feature[(size_t)R] >= 0) visit(R, depth + 1, units, list, out);
+    ops.push_back(WalkOp{M_->feature[(size_t)node], walk_key_bits(b) - bias, (uint32_t)drop | (bias ? kWalkBias : 0u), 0u});
   }
 
   const wdf_model *M_;
-  std::vector<int64_t> mark_, at_;
-  int64_t stamp_ = 0, base_ = 0;
-  int have_ = 0;  // splits in P
 };
 
-template <class T>
-int upload(DevBuf &buf, const std::vector<T> &v, hipStream_t s) {
-  const int rc = buf.alloc(std::max<size_t>(v.size(), 1) * sizeof(T));
-  if (rc || v.empty()) return rc;
-  HIP_TRY(hipMemcpyAsync(buf.ptr, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  return WDF_OK;
-}
+// Arrays of one plan, copied into one device buffer: *ptr receives each one's
+// address.  One allocation and one wait instead of one per array (a model of 10
+// trees spent most of its load on them).
+class Upload {
+ public:
+  template <class T>
+  void add(const std::vector<T> &v, const T *&ptr) {
+    parts_.push_back({v.data(), v.size() * sizeof(T), bytes_, (const void **)&ptr});
+    bytes_ += (v.size() * sizeof(T) + 255) / 256 * 256;
+  }
+  int run(DevBuf &buf, hipStream_t s) {
+    const int rc = buf.alloc(std::max<size_t>(bytes_, 256));
+    if (rc) return rc;
+    for (const Part &p : parts_) {
+      *p.ptr = (const char *)buf.ptr + p.at;
+      if (p.bytes) HIP_TRY(hipMemcpyAsync((char *)buf.ptr + p.at, p.src, p.bytes, hipMemcpyHostToDevice, s));
+    }
+    HIP_TRY(hipStreamSynchronize(s));
+    return WDF_OK;
+  }
+
+ private:
+  struct Part {
+    const void *src;
+    size_t bytes, at;
+    const void **ptr;
+  };
+  std::vector<Part> parts_;
+  size_t bytes_ = 0;
+};
 
 // unit of a group's own table (no quad)
 WalkUnit group_unit(const wdf_model *M, int64_t g, uint32_t mask) {
@@ -162,13 +165,24 @@ int build_level(const wdf_model *M, const std::vector<WalkUnit> &units, const st
   std::vector<WalkRun> runs;
   std::vector<WalkEntry> entries;
   std::vector<int32_t> slot(units.size(), -1);
+  size_t total = 0;
+  for (const ColumnGroup &cg : groups)
+    for (const auto &l : cg.lists) total += l.second->size();
+  entries.reserve(total);
   int most = 0;
   for (const ColumnGroup &cg : groups) {
+    // the units of the group's columns, in order
     std::vector<int32_t> need;
     for (const auto &l : cg.lists)
-      for (const ColumnEntry &e : *l.second) need.push_back(e.unit);
-    std::sort(need.begin(), need.end());
-    need.erase(std::unique(need.begin(), need.end()), need.end());
+      for (const ColumnEntry &e : *l.second)
+        if (slot[(size_t)e.unit] != -2) slot[(size_t)e.unit] = -2, need.push_back(e.unit);
+    if (need.size() < units.size() / 16) {
+      std::sort(need.begin(), need.end());
+    } else {
+      need.clear();
+      for (size_t u = 0; u < units.size(); ++u)
+        if (slot[u] == -2) need.push_back((int32_t)u);
+    }
     WalkGroup wg{cg.col0, (int32_t)chunks.size(), 0};
     std::vector<size_t> at(cg.lists.size(), 0);
     for (size_t a = 0; a == 0 || a < need.size(); a += (size_t)cap) {
@@ -216,13 +230,14 @@ int build_level(const wdf_model *M, const std::vector<WalkUnit> &units, const st
   out.max_column = 0;
   for (const ColumnGroup &cg : groups)
     for (const auto &l : cg.lists) out.max_column = std::max(out.max_column, (int64_t)l.second->size());
-  hipStream_t s = M->ctx->stream;
-  int rc;
-  if ((rc = upload(out.ops, prog.ops, s)) || (rc = upload(out.segs, prog.segs, s)) ||
-      (rc = upload(out.groups, gs, s)) || (rc = upload(out.chunks, chunks, s)) || (rc = upload(out.runs, runs, s)) ||
-      (rc = upload(out.entries, entries, s)))
-    return rc;
-  return WDF_OK;
+  Upload up;
+  up.add(prog.ops, out.ops);
+  up.add(prog.segs, out.segs);
+  up.add(gs, out.groups);
+  up.add(chunks, out.chunks);
+  up.add(runs, out.runs);
+  up.add(entries, out.entries);
+  return up.run(out.buf, M->ctx->stream);
 }
 
 }  // namespace
@@ -237,8 +252,10 @@ static int build_explain(wdf_model *M) {
   JitPlan &P = M->jp;
   const int F = M->n_features;
   int rc;
-  if ((rc = upload(P.d_xunits, P.xunits, M->ctx->stream)) || (rc = upload(P.d_unit_g0, P.unit_g0, M->ctx->stream)))
-    return rc;
+  Upload up;
+  up.add(P.xunits, P.d_xunits);
+  up.add(P.unit_g0, P.d_unit_g0);
+  if ((rc = up.run(P.d_units, M->ctx->stream))) return rc;
   std::vector<WalkUnit> units;
   std::vector<std::vector<ColumnEntry>> cols((size_t)F);
   bool wide = false;
@@ -357,12 +374,12 @@ static int build_hist(wdf_model *M) {
   WalkHist &W = M->walk_hist;
   W.n_chunks = (int)chunks.size();
   W.n_roots = (int)roots.size();
-  hipStream_t s = M->ctx->stream;
-  int rc;
-  if ((rc = upload(W.ops, prog.ops, s)) || (rc = upload(W.segs, prog.segs, s)) || (rc = upload(W.chunks, chunks, s)) ||
-      (rc = upload(W.roots, roots, s)))
-    return rc;
-  return WDF_OK;
+  Upload up;
+  up.add(prog.ops, W.ops);
+  up.add(prog.segs, W.segs);
+  up.add(chunks, W.chunks);
+  up.add(roots, W.roots);
+  return up.run(W.buf, M->ctx->stream);
 }
 
 int walk_build_explain(wdf_model *M) {
@@ -379,9 +396,8 @@ int walk_hist(const wdf_model *M, const float *B, int64_t m, int64_t ldb, uint32
   const WalkHist &W = M->walk_hist;
   const int most = 65535;  // chunks of one launch (grid.y)
   for (int c0 = 0; c0 < W.n_chunks; c0 += most) {
-    const HistWalkArgs a{B, ldb, m, hist, W.ops.as<WalkOp>(), W.segs.as<int2>(), W.chunks.as<WalkHistChunk>() + c0,
-                         W.roots.as<int64_t>(), std::min(most, W.n_chunks - c0), c0 ? 0 : W.n_roots, M->n_features,
-                         M->ctx->n_cu};
+    const HistWalkArgs a{B, ldb, m, hist, W.ops, W.segs, W.chunks + c0, W.roots, std::min(most, W.n_chunks - c0),
+                         c0 ? 0 : W.n_roots, M->n_features, M->ctx->n_cu};
     HIP_TRY(launch_hist_walk(a, s));
   }
   return WDF_OK;
@@ -394,8 +410,7 @@ static int walk_launch(const wdf_model *M, const WalkLevel &L, const float *tab,
   const int64_t blocks = 2 * (int64_t)M->ctx->n_cu;
   int rows = 1;
   while (rows < 64 && (n + rows - 1) / rows * L.n_groups > blocks) rows *= 4;
-  const WalkArgs a{X, ldx, n, out, ldo, tab, L.ops.as<WalkOp>(), L.segs.as<int2>(), L.groups.as<WalkGroup>(),
-                   L.chunks.as<WalkChunk>(), L.runs.as<WalkRun>(), L.entries.as<WalkEntry>(), M->n_features, 0};
+  const WalkArgs a{X, ldx, n, out, ldo, tab, L.ops, L.segs, L.groups, L.chunks, L.runs, L.entries, M->n_features, 0};
   HIP_TRY(launch_walk(a, L.n_groups, L.max_slots, L.wide, L.entry_shift, rows, s));
   return WDF_OK;
 }
