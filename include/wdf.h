@@ -306,7 +306,9 @@ int wdf_debug_time_contraction(const wdf_bg *bg, int reps, void *hip_stream, dou
  * memory) / the float tables (step (f)) to the host.  With host_out NULL,
  * only the entry count is returned.  Returns the number of entries, or
  * INVALID_ARG (NULL summary, cap too small, a path-dependent summary for the
- * histograms) or DEVICE. */
+ * histograms) or DEVICE.  A generic model's summary holds no gather tables:
+ * wdf_debug_tables computes them from the histograms, in memory of the call
+ * (OOM). */
 int64_t wdf_debug_histograms(const wdf_bg *bg, uint32_t *host_out, int64_t cap);
 int64_t wdf_debug_tables(const wdf_bg *bg, float *host_out, int64_t cap);
 

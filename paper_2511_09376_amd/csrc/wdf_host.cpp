@@ -658,16 +658,17 @@ static int prepare_iv(wdf_model *M, int kind) {
 
 // Table storage of a summary, zeroed once (the padding between tables, and the
 // 256 floats after the interaction tables that padding items read, are never
-// written again).
+// written again); the explain tables are written whole.  Explain calls read
+// the explain tables alone, so a generic model's summary holds no gather tables
+// beside them (wdf_debug_tables computes them).
 static int alloc_tables(wdf_model *M, wdf_bg *bg, hipStream_t s) {
   int rc;
-  const int64_t n = bg->iv ? M->iv_tab_size + 256 : M->tab_size;
-  if ((rc = bg->d_tab.alloc((size_t)std::max<int64_t>(n, 1) * sizeof(float)))) return rc;
-  HIP_TRY(hipMemsetAsync(bg->d_tab.ptr, 0, bg->d_tab.bytes, s));
-  if (!bg->iv) {
-    if ((rc = bg->d_xtab.alloc((size_t)std::max<int64_t>(M->jp.xtab_size, 1) * sizeof(float)))) return rc;
-    HIP_TRY(hipMemsetAsync(bg->d_xtab.ptr, 0, bg->d_xtab.bytes, s));
+  if (bg->iv || M->jit) {
+    const int64_t n = bg->iv ? M->iv_tab_size + 256 : M->tab_size;
+    if ((rc = bg->d_tab.alloc((size_t)std::max<int64_t>(n, 1) * sizeof(float)))) return rc;
+    HIP_TRY(hipMemsetAsync(bg->d_tab.ptr, 0, bg->d_tab.bytes, s));
   }
+  if (!bg->iv && (rc = bg->d_xtab.alloc((size_t)std::max<int64_t>(M->jp.xtab_size, 1) * sizeof(float)))) return rc;
   if (bg->iv_spec) {
     if ((rc = bg->d_xtab.alloc((size_t)std::max<int64_t>(M->iv_units_size, 1) * sizeof(float)))) return rc;
     HIP_TRY(hipMemsetAsync(bg->d_xtab.ptr, 0, bg->d_xtab.bytes, s));
@@ -700,9 +701,10 @@ static int enqueue_gemms(wdf_model *M, const wdf_bg *bg, const double *H, double
 }
 
 // Columns, MFMA products per class, expansion into the gather tables (and the
-// explain tables), base value into *base: kernel launches only.
-static int enqueue_contract(wdf_model *M, wdf_bg *bg, const uint32_t *hist, const double *freq, double scale,
-                            double *H, double *S, double *base, hipStream_t s) {
+// explain tables) of the summary or of the caller, base value into *base:
+// kernel launches only.  tab may be NULL unless the summary holds interactions.
+static int enqueue_contract(wdf_model *M, const wdf_bg *bg, const uint32_t *hist, const double *freq, double scale,
+                            double *H, double *S, float *tab, float *xtab, double *base, hipStream_t s) {
   const int64_t G = (int64_t)M->groups.size();
   const double *freq_r = freq ? freq + M->hist_size : nullptr;  // right leaves' own frequencies
   HIP_TRY(launch_columns(M->d_groups.as<Group>(), M->d_path.as<PathNode>(), G, hist, freq, freq_r, scale,
@@ -712,10 +714,9 @@ static int enqueue_contract(wdf_model *M, wdf_bg *bg, const uint32_t *hist, cons
     int rc;
     if ((rc = enqueue_gemms(M, bg, H, S, s, nullptr))) return rc;
     HIP_TRY(launch_expand_iv(M->d_groups.as<Group>(), M->d_path.as<PathNode>(), G, M->d_iv_off.as<int64_t>(),
-                             M->d_siv_class_off.as<int64_t>(), S, bg->d_tab.as<float>(), s));
+                             M->d_siv_class_off.as<int64_t>(), S, tab, s));
     if (bg->iv_spec)  // interleaved tables of the specialised interaction kernel
-      HIP_TRY(launch_ivtab(M->d_iv_units.as<IvUnit>(), (int64_t)M->iv_units.size(), bg->d_tab.as<float>(),
-                           bg->d_xtab.as<float>(), s));
+      HIP_TRY(launch_ivtab(M->d_iv_units.as<IvUnit>(), (int64_t)M->iv_units.size(), tab, xtab, s));
     HIP_TRY(launch_base(base_args, s));
     return WDF_OK;
   }
@@ -723,7 +724,7 @@ static int enqueue_contract(wdf_model *M, wdf_bg *bg, const uint32_t *hist, cons
   if ((rc = enqueue_gemms(M, bg, H, S, s, nullptr))) return rc;
   HIP_TRY(launch_tables(M->jp.d_xunits, M->jp.d_unit_g0, (int64_t)M->jp.xunits.size(),
                         M->d_groups.as<Group>(), M->d_path.as<PathNode>(), M->d_sclass_off.as<int64_t>(), S,
-                        bg->d_tab.as<float>(), bg->d_xtab.as<float>(), base_args, s));
+                        tab, xtab, base_args, s));
   return WDF_OK;
 }
 
@@ -738,7 +739,8 @@ static int contract(wdf_model *M, wdf_bg *bg, const uint32_t *hist, const double
     return rc;
   if ((rc = ws_reserve(base, sizeof(double)))) return rc;
   if ((rc = alloc_tables(M, bg, s))) return rc;
-  if ((rc = enqueue_contract(M, bg, hist, freq, scale, H.as<double>(), S.as<double>(), base.as<double>(), s)))
+  if ((rc = enqueue_contract(M, bg, hist, freq, scale, H.as<double>(), S.as<double>(), bg->d_tab.as<float>(),
+                             bg->d_xtab.as<float>(), base.as<double>(), s)))
     return rc;
   HIP_TRY(hipMemcpyAsync(&bg->base, base.ptr, sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
@@ -829,7 +831,8 @@ static int enqueue_refresh(wdf_bg *bg, const float *B, int64_t ldb, hipStream_t 
     if ((rc = walk_hist(M, B, m, ldb, bg->d_hist.as<uint32_t>(), s))) return rc;
   }
   return enqueue_contract(M, bg, bg->d_hist.as<uint32_t>(), nullptr, 1.0 / (double)m, bg->own_H.as<double>(),
-                          bg->own_S.as<double>(), bg->d_base.as<double>(), s);
+                          bg->own_S.as<double>(), bg->d_tab.as<float>(), bg->d_xtab.as<float>(), bg->d_base.as<double>(),
+                          s);
 }
 
 static int check_refresh(const wdf_bg *bg, const float *B, int64_t ldb, const char *who) {
@@ -1146,7 +1149,26 @@ extern "C" int64_t wdf_debug_tables(const wdf_bg *bg, float *host_out, int64_t c
     if (cap < n) return set_error(WDF_E_INVALID_ARG, "wdf_debug_tables: capacity %lld < %lld", (long long)cap,
                                   (long long)n);
     HIP_TRY(hipSetDevice(bg->model->ctx->device));
-    HIP_TRY(hipMemcpy(host_out, bg->d_tab.ptr, (size_t)n * sizeof(float), hipMemcpyDeviceToHost));
+    const float *tab = bg->d_tab.as<float>();
+    DevBuf H, S, own, xtab, base;
+    if (!tab && n > 0) {  // a generic model's: contracted again from the histograms, into buffers of this call
+      wdf_model *M = bg->model;
+      int rc;
+      if ((rc = H.alloc((size_t)std::max<int64_t>(M->h_total, 1) * sizeof(double))) ||
+          (rc = S.alloc((size_t)std::max<int64_t>(M->s_total, 1) * sizeof(double))) ||
+          (rc = own.alloc((size_t)n * sizeof(float))) ||
+          (rc = xtab.alloc((size_t)std::max<int64_t>(M->jp.xtab_size, 1) * sizeof(float))) ||
+          (rc = base.alloc(sizeof(double))))
+        return rc;
+      HIP_TRY(hipMemset(own.ptr, 0, own.bytes));
+      if ((rc = enqueue_contract(M, bg, bg->pathdep ? nullptr : bg->d_hist.as<uint32_t>(),
+                                 bg->pathdep ? bg->d_hist.as<double>() : nullptr,
+                                 bg->pathdep ? 1.0 : 1.0 / (double)bg->m, H.as<double>(), S.as<double>(),
+                                 own.as<float>(), xtab.as<float>(), base.as<double>(), nullptr)))
+        return rc;
+      tab = own.as<float>();
+    }
+    if (n > 0) HIP_TRY(hipMemcpy(host_out, tab, (size_t)n * sizeof(float), hipMemcpyDeviceToHost));
   }
   return n;
 }

@@ -243,7 +243,7 @@ struct wdf_bg {
   double base = 0.0;
   wdf::DevBuf d_hist;   // uint32 counts (background) or double frequencies (path-dependent: the left or
                         // single leaves' [hist_size], then the right leaves' [hist_size])
-  wdf::DevBuf d_tab;    // float gather tables
+  wdf::DevBuf d_tab;    // float gather tables (of a specialised model) or interaction tables
   wdf::DevBuf d_xtab;   // explain tables (quads merged), or the interleaved interaction tables (iv_spec)
   bool iv_spec = false; // interaction summary explained by the specialised kernel
   // private workspace of in-place refreshes (allocated by the first one):

@@ -74,7 +74,7 @@ struct BaseArgs {
   double *out;
 };
 hipError_t launch_base(const BaseArgs &b, hipStream_t s);
-// gather tables, explain tables and the base value; unit_g0: first group of every unit
+// gather tables (tab null: none), explain tables and the base value; unit_g0: first group of every unit
 hipError_t launch_tables(const XUnit *units, const int64_t *unit_g0, int64_t n_units, const Group *groups,
                          const PathNode *path, const int64_t *s_class_off, const double *S, float *tab, float *xtab,
                          const BaseArgs &base, hipStream_t s);

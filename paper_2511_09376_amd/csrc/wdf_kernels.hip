@@ -903,8 +903,8 @@ hipError_t launch_explain_iv(const Group *groups, const PathNode *path, int64_t 
   return hipGetLastError();
 }
 
-// Gather and explain tables of one unit (a group, or the two pair groups of a
-// quad), and in the last block the base value.
+// Gather (unless tab is null) and explain tables of one unit (a group, or the
+// two pair groups of a quad), and in the last block the base value.
 //
 // Gather tables: tab[g][k][p] = S_l[merge(k)][g(p)] + S_r[merge(k)][g(p ^ 1)]
 // at the first position of each feature on the path, 0 at later repeats.  A
@@ -957,7 +957,7 @@ __global__ __launch_bounds__(256) void k_tables(const XUnit *__restrict__ units,
         if (g.col_r >= 0) v += Sr[row + mr];
       }
       t[h][(k << d) + p] = (float)v;
-      tab[g.tab_off + (k << d) + p] = (float)v;
+      if (tab) tab[g.tab_off + (k << d) + p] = (float)v;
     }
   }
   __syncthreads();

@@ -1,6 +1,7 @@
 """What a model without generated kernels pays for before its first values: the
 load plans its walks and nothing for the LDS, and a summary holds its tables
 once."""
+import re
 import time
 
 import pytest
@@ -33,3 +34,31 @@ def test_generic_load_time(uneven):
         model.close()
     print(f"generic load {1e3 * best:.1f} ms", flush=True)
     assert best < 15.5e-3
+
+
+def test_generic_summary_holds_its_tables_once(uneven):
+    wdf, ctx, w, ens = uneven
+    tab_bytes = int(re.search(r"#define TAB_BYTES (\d+)", wdf.specialised_source(ens)).group(1))
+    model = wdf.Model(ctx, ens, wdf.KERNEL_GENERIC)
+    B = torch.from_numpy(w.background(3000)).cuda()
+    keep = [wdf.Background(model, B)]                     # (the model's workspace is allocated with the first)
+    hist, tables = 4 * keep[0].histograms().size, keep[0].tables()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    keep += [wdf.Background(model, B) for _ in range(8)]
+    each = (free - torch.cuda.mem_get_info()[0]) / 8
+    print(f"summary {each:.0f} bytes: histograms {hist}, explain tables {tab_bytes}, gather tables {tables.nbytes}", flush=True)
+    assert each <= hist + tab_bytes + tables.nbytes / 2
+    assert (keep[8].tables() == tables).all()
+    # the tables on demand: those of the specialised model's summary, also after a refresh and path-dependent
+    small = synth.WORKLOADS["small"]
+    e2, B2, C2 = small.ensemble(), torch.from_numpy(small.background()).cuda(), torch.from_numpy(small.consumers()).cuda()
+    ms, mg = wdf.Model(ctx, e2, wdf.KERNEL_SPECIALISED), wdf.Model(ctx, e2, wdf.KERNEL_GENERIC)
+    a, b = wdf.Background(ms, B2, values=wdf.BANZHAF), wdf.Background(mg, B2, values=wdf.BANZHAF)
+    before = b.explain(C2)
+    assert (a.tables() == b.tables()).all() and torch.equal(b.explain(C2), before)
+    a.refresh(C2), b.refresh(C2)
+    torch.cuda.synchronize()
+    assert (a.tables() == b.tables()).all() and a.base_value == b.base_value
+    a, b = wdf.Background(ms, pathdep=True), wdf.Background(mg, pathdep=True)
+    assert (a.tables() == b.tables()).all()
