@@ -19,7 +19,22 @@ struct HistWalkArgs {
   const int64_t *root_bins;
   int n_chunks, n_root_bins, F, n_cu;
 };
-constexpr int kHistWalkBins = 12288;  // bins of a chunk in LDS (48 KB: with the row keys two blocks fit a CU)
+constexpr int kWalkXFeatures = 160;  // row keys staged in LDS up to this many features (64 rows: 40 KB)
+// LDS of the data-driven histogram: a chunk's bins and 64 rows' keys, so that
+// two blocks fit a CU: 12288 bins up to 128 features, fewer up to 160 (refresh of
+// 500 uneven trees of 150 features, 100k rows: 7.65 ms with 12288 bins and the
+// one block per CU that fits then, 5.22 with 10880; of 128 features 4.31)
+constexpr int hist_walk_key_bytes(int F) { return F <= kWalkXFeatures ? F * 64 * 4 : 0; }
+constexpr int hist_walk_bins(int F) {
+  const int fit = (80 * 1024 - hist_walk_key_bytes(F)) / 4;
+  return fit < 12288 ? fit : 12288;
+}
+constexpr bool hist_walk_two_blocks_fit() {
+  for (int F = 1; F <= kWalkXFeatures + 1; ++F)
+    if (2 * (hist_walk_bins(F) * 4 + hist_walk_key_bytes(F)) > 160 * 1024) return false;
+  return true;
+}
+static_assert(hist_walk_two_blocks_fit(), "launch_hist_walk plans two blocks per CU");
 hipError_t launch_hist_walk(const HistWalkArgs &a, hipStream_t s);
 // The data-driven gather: column c of out (out[c * ldo + row]) is the sum of
 // its table entries.

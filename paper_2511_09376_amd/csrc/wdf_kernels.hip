@@ -40,7 +40,6 @@ __device__ __forceinline__ uint32_t group_pattern(const Group &g, const PathNode
 // CUs.
 
 constexpr int kWalkThreads = 512, kWalkWaves = kWalkThreads / 64;
-constexpr int kWalkXFeatures = 160;  // row keys staged in LDS up to this many features (40 KB)
 
 __device__ __forceinline__ uint32_t walk_key(float x) { return walk_key_bits(__float_as_uint(x)); }
 
@@ -100,7 +99,7 @@ __device__ __forceinline__ void walk_segment(const WalkOp *__restrict__ ops, int
 __global__ __launch_bounds__(kWalkThreads) void k_hist_walk(const HistWalkArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t wsmem[];
   uint32_t *bins = wsmem;
-  uint32_t *xt = a.F <= kWalkXFeatures ? wsmem + kHistWalkBins : nullptr;
+  uint32_t *xt = a.F <= kWalkXFeatures ? wsmem + hist_walk_bins(a.F) : nullptr;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const WalkHistChunk ch = a.chunks[blockIdx.y];
   for (int i = threadIdx.x; i < ch.bins; i += kWalkThreads) bins[i] = 0u;
@@ -505,7 +504,7 @@ hipError_t launch_hist_walk(const HistWalkArgs &a, hipStream_t s) {
     const int64_t cost = (q * a.n_chunks + slots - 1) / slots * ((tiles + q - 1) / q + 2);
     if (best < 0 || cost < best) best = cost, per = q;
   }
-  const size_t lds = (size_t)kHistWalkBins * 4 + (a.F <= kWalkXFeatures ? (size_t)a.F * 256 : 0);
+  const size_t lds = (size_t)hist_walk_bins(a.F) * 4 + (size_t)hist_walk_key_bytes(a.F);
   hipLaunchKernelGGL(k_hist_walk, dim3((unsigned)per, (unsigned)a.n_chunks),
                      dim3(kWalkThreads), lds, s, a);
   return hipGetLastError();

@@ -354,11 +354,12 @@ static int build_hist(wdf_model *M) {
     if (M->groups[(size_t)g].depth == 0) roots.push_back(M->groups[(size_t)g].hist_off);
     else units[(size_t)g] = group_unit(M, g, right_turns(M, M->groups[(size_t)g]));
   }
+  const int64_t bins = hist_walk_bins(M->n_features);
   for (int64_t g = 0; g < G;) {
     const int64_t bin0 = M->groups[(size_t)g].hist_off;
     list.clear();
     int64_t end = bin0;
-    for (; g < G && end - bin0 + ((int64_t)1 << M->groups[(size_t)g].depth) <= kHistWalkBins; ++g) {
+    for (; g < G && end - bin0 + ((int64_t)1 << M->groups[(size_t)g].depth) <= bins; ++g) {
       end += (int64_t)1 << M->groups[(size_t)g].depth;
       if (M->groups[(size_t)g].depth) list.push_back((int32_t)g);
     }

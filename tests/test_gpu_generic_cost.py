@@ -62,3 +62,17 @@ def test_generic_summary_holds_its_tables_once(uneven):
     assert (a.tables() == b.tables()).all() and a.base_value == b.base_value
     a, b = wdf.Background(ms, pathdep=True), wdf.Background(mg, pathdep=True)
     assert (a.tables() == b.tables()).all()
+
+
+@pytest.mark.parametrize("F", [128, 129, 150, 160, 161])
+def test_generic_histograms_by_features(uneven, F):
+    """The bins of a block and its row keys share the LDS: several chunks of
+    bins at the limits of both, every count that of the specialised model."""
+    wdf, ctx, _, _ = uneven
+    data = synth.DataSpec(F, True, 0.05)
+    ens = synth.make_ensemble(synth.ModelSpec(40, 5, 8, 0.1, F), data, F)
+    X = torch.from_numpy(synth.make_matrix(data, 1000, 8)).cuda()
+    gen = wdf.Model(ctx, ens, wdf.KERNEL_GENERIC)
+    a, b = wdf.Background(gen, X), wdf.Background(wdf.Model(ctx, ens, wdf.KERNEL_SPECIALISED), X)
+    assert a.histograms().size > 2 * 12288
+    assert (a.histograms() == b.histograms()).all()
