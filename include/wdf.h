@@ -358,7 +358,8 @@ typedef struct {
                                  launch bound the model's histogram kernel was compiled for) */
   float explain_ms[WDF_MAX_DEPTH + 1];  /* explain time per quads value, 512-row tiles */
   float explain_rows_ms[2];   /* explain time with the chosen gather: [0] 512-row, [1] 256-row tiles */
-  float hist_ms[3][9];        /* histogram time with [512, 768, 1024 threads][hist_rounds = 1..8] */
+  float hist_ms[3][9];        /* histogram time with [512, 768, 1024 threads][hist_rounds = 1..8]
+                                 (settings that launch the same grid share one time) */
 } wdf_tuning;
 
 /* Measure the model's specialised kernels on the caller's data and keep the

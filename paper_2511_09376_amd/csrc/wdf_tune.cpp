@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <memory>
 #include <string>
 #include <vector>
@@ -64,7 +65,9 @@ extern "C" int wdf_model_autotune(wdf_model *M, const float *B, int64_t m, int64
   int rc = WDF_OK;
 
   // histogram grid and block size: launch-time choices, timed on one
-  // histogram buffer
+  // histogram buffer.  Where a wave has few tiles several settings launch the
+  // same grid: it is timed once, and the rounds the model had are kept when
+  // they launch the fastest one.
   {
     DevBuf hist, codes;
     if ((rc = hist.alloc((size_t)std::max<int64_t>(M->hist_size, 1) * sizeof(uint32_t)))) return rc;
@@ -74,12 +77,20 @@ extern "C" int wdf_model_autotune(wdf_model *M, const float *B, int64_t m, int64
     float best_ms = -1.f;
     const int threads[3] = {512, 768, 1024};
     static_assert(kHistMaxThreads == 1024, "the sweep covers blocks up to the largest launch bound");
+    auto launch_of = [&](int t, int r) {
+      M->jp.nt_hist = t;
+      M->jp.hist_rounds = r;
+      const HistLaunch L = hist_launch(M, m);
+      return std::array<int64_t, 3>{L.threads, L.blocks, L.tiles_per_block};
+    };
+    std::array<std::pair<std::array<int64_t, 3>, float>, 18> timed;  // grids and their times
+    auto end = timed.begin();
     for (int ti = 0; ti < 3; ++ti) {
       if (threads[ti] > M->jp.hist_bound) continue;  // beyond the compiled launch bound
       for (int r : {1, 2, 3, 4, 6, 8}) {
-        M->jp.nt_hist = threads[ti];
-        M->jp.hist_rounds = r;
-        const float ms = time_runs(
+        const auto L = launch_of(threads[ti], r);
+        const auto seen = std::find_if(timed.begin(), end, [&](const auto &t) { return t.first == L; });
+        const float ms = seen != end ? seen->second : time_runs(
             s, reps, [&] { return jit_hist(M, B, m, ldb, hist.as<uint32_t>(), codes.as<uint32_t>(), s); }, rc);
         if (rc) {
           M->jp.hist_rounds = keep_r;
@@ -87,8 +98,13 @@ extern "C" int wdf_model_autotune(wdf_model *M, const float *B, int64_t m, int64
           return rc;
         }
         out->hist_ms[ti][r] = ms;
+        if (seen == end) *end++ = {L, ms};
         if (best_ms < 0.f || ms < best_ms) best_ms = ms, best_r = r, best_t = threads[ti];
       }
+    }
+    if (keep_r <= 8 && launch_of(best_t, keep_r) == launch_of(best_t, best_r)) {
+      best_r = keep_r;
+      out->hist_ms[best_t / 256 - 2][best_r] = best_ms;
     }
     M->jp.hist_rounds = best_r;
     M->jp.nt_hist = best_t;

@@ -71,3 +71,25 @@ def test_autotune_refusals(wdf, ctx):
     generic = wdf.Model(ctx, ens, wdf.KERNEL_GENERIC)
     with pytest.raises(wdf.WdfError):
         generic.autotune(Bd, Xd)
+
+
+def test_settings_of_one_grid_are_timed_once(wdf, ctx):
+    """On a small sample most rounds launch one grid: one time for all of them,
+    and the rounds the model had (2) stay when they launch the fastest."""
+    w = synth.WORKLOADS["mid"]
+    m = 5003
+    Bd, Xd = torch.from_numpy(w.background(m)).cuda(), torch.from_numpy(w.consumers(500)).cuda()
+    model = wdf.Model(ctx, w.ensemble(), wdf.KERNEL_SPECIALISED)
+    rep = model.autotune(Bd, Xd)
+    times = {}
+    for key, ms in rep["hist_ms"].items():
+        nt, r = (int(x) for x in key.split("x"))
+        model.set_tuning({"hist_threads": nt, "hist_rounds": r})
+        L = model.hist_launch(m)
+        times.setdefault((nt, L["blocks"], L["tiles_per_block"]), {})[r] = ms
+    assert len(times) < len(rep["hist_ms"])
+    for grid, by_rounds in times.items():
+        assert len(set(by_rounds.values())) == 1, (grid, by_rounds)
+        if (rep["hist_threads"], rep["hist_rounds"]) in ((grid[0], r) for r in by_rounds) and 2 in by_rounds:
+            assert rep["hist_rounds"] == 2
+    assert rep["hist_ms"][f"{rep['hist_threads']}x{rep['hist_rounds']}"] <= min(rep["hist_ms"].values())
