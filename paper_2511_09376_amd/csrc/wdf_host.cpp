@@ -993,7 +993,7 @@ static bool may_share(const float *a, int64_t lda, int64_t rows_a, const float *
 Route wdf::explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *phi, int64_t ldphi) {
   const wdf_model *M = bg->model;
   if (!M->jit) return Route::gather;
-  if (n > kWalkMaxRows || (int)M->jp.explain_stages.size() <= kFewStages) return Route::generated;
+  if (n > kWalkMaxRows || (int)M->jp.explain_stages.size() <= kFewStages || M->walk.empty()) return Route::generated;
   if (2 * M->walk.front()->max_column > (int64_t)M->jp.xunits.size() && 4 * M->jp.xtab_size <= kBusyColumnTables)
     return Route::generated;
   return may_share(X, ldx, M->n_features, phi, ldphi, M->n_features, n) ? Route::generated : Route::gather;
