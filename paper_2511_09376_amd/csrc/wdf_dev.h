@@ -40,8 +40,7 @@ struct Group {
 // returns four values of an entry; entry I sits at slot
 // I ^ (I >> fold_a) ^ (I >> fold_b) of each plane (a bijection), the shifts
 // chosen per unit so that the entries rows are likely to read together fall
-// in different groups of LDS banks (none for models without generated kernels,
-// whose tables are read from global memory).
+// in different groups of LDS banks.
 struct XUnit {
   int64_t dst;     // offset in the explain tables (floats, multiple of 4)
   int32_t depth;   // depth of the group(s)

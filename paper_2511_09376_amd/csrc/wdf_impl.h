@@ -296,8 +296,8 @@ enum class Route { generated = 0, gather = 1, listed = 2 };
 Route explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *phi, int64_t ldphi);
 Route explain_iv_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *iv, int64_t ldiv);
 // the explain-table units of the model, none larger than max_floats as a quad,
-// with or without a fold for the LDS banks (wdf_jit.cpp)
-void plan_units(wdf_model *M, int64_t max_floats, bool folds);
+// their folds searched for the generated explain kernel or default (wdf_jit.cpp)
+void plan_units(wdf_model *M, int64_t max_floats, bool generated);
 // Data-driven kernels (wdf_walk.cpp): the plan of the explain walk for the
 // planned units (which it uploads), and of the histogram
 int walk_build_explain(wdf_model *M);

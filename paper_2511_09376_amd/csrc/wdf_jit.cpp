@@ -81,11 +81,18 @@ namespace {
 // the group (the chance that two reads hit one group, up to a term no fold
 // changes).  Shifts come from ancestors' patterns: at least 1 for a group, 2
 // for a quad (whose index has no register for I >> 1).  Without covers, or on
-// a tie: shifts 3 and 6 where below the index width.
-void choose_fold(const wdf_model *M, XUnit &u, int64_t tree, const std::vector<int64_t> &nodes) {
+// a tie, the default: shifts 3 and 6 where below the index width.  Models
+// without generated kernels keep the default: the search is most of their load
+// (500 uneven trees 31 ms against 6.6), and the gather's reads of global memory
+// run the same on both (100k rows 12.37 and 12.36 ms; unfolded 13.16).
+void default_fold(XUnit &u) {
   const int bits = u.depth + u.quad;
   u.fold_a = bits > 3 ? 3 : 0;
   u.fold_b = bits > 6 ? 6 : 0;
+}
+
+void choose_fold(const wdf_model *M, XUnit &u, int64_t tree, const std::vector<int64_t> &nodes) {
+  const int bits = u.depth + u.quad;
   if (!M->has_cover || bits <= 4) return;  // up to 16 entries sit in distinct groups whatever the fold
   const int E = 1 << bits;
   const int64_t base = M->node_offset[(size_t)tree];
@@ -115,7 +122,7 @@ void choose_fold(const wdf_model *M, XUnit &u, int64_t tree, const std::vector<i
 
 }  // namespace
 
-void plan_units(wdf_model *M, int64_t max_floats, bool folds) {
+void plan_units(wdf_model *M, int64_t max_floats, bool generated) {
   JitPlan &P = M->jp;
   const int64_t G = (int64_t)M->groups.size();
   // explain-table units: a pair group and the next pair group form a quad
@@ -146,7 +153,8 @@ void plan_units(wdf_model *M, int64_t max_floats, bool folds) {
     u.mask = 0;
     for (int k = 0; k < (quad ? ga.depth - 2 : ga.depth); ++k)
       u.mask = (u.mask << 1) | M->path[(size_t)ga.path_off + (size_t)k].dir;
-    if (folds) {
+    default_fold(u);
+    if (generated) {
       // the nodes of the index bits: the group's path (and for a quad the
       // right pair's node last)
       std::vector<int64_t> nodes;
