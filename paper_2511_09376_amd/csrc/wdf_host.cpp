@@ -1006,7 +1006,7 @@ Route wdf::explain_iv_route(const wdf_bg *bg, const float *X, int64_t n, int64_t
   const bool few = L && ((n <= kWalkIvRows && 2 * tiles <= 7 * n_cu) ||
                          (work <= kWalkIvWork && n * L->max_column <= kWalkIvColumn));
   if (few && !may_share(X, ldx, F, iv, ldiv, F * F, n)) return Route::gather;
-  return bg->iv_spec && work > iv_listed_work(M->n_nodes, F, M->iv_longest) ? Route::generated : Route::listed;
+  return bg->iv_spec && work > iv_listed_work(M->iv_values, M->iv_longest) ? Route::generated : Route::listed;
 }
 
 extern "C" int wdf_debug_explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *out,

@@ -142,18 +142,16 @@ constexpr int64_t kBusyColumnTables = 3 << 20;
 // features (990 entries in a column), 1024 rows 111 / 179 / 131, 2048 rows
 // 136 / 157 / 119.
 constexpr int64_t kWalkIvRows = 512, kWalkIvWork = 16 << 20, kWalkIvColumn = 1 << 20;
-// The lists: fast while the longest is short beside what the generated kernels
-// take for any number of rows (which grows with the nodes and the features);
-// per value the generated kernels add faster.  Largest work of each side's
-// advantage, millions, measured / this line: 20 depth-6 trees of 127 features
-// 135 / 138, 60 of them 313 / 263, 100 of them 430 / 394, 30 of 200 features
-// 183 / 195, 30 of 60 features 144 / 89, 60 depth-5 trees of 30 features
-// 120 / 90, 100 depth-4 trees of 16 features 92 / 75; lists over 1000 of 4 to 16
-// features none / below 16 (40 depth-6 trees of 8 features, 8192 rows 289
-// listed, 160 generated).
-inline int64_t iv_listed_work(int64_t n_nodes, int64_t n_features, int64_t longest) {
-  return 1000 * (30000 + 37 * n_nodes + 500 * n_features - 130 * longest);
-}
+// The lists: their time is the longest one's walk plus the work, that of the
+// generated kernels what their launches and table streams take for any number
+// of rows (which grows with the values) plus less per value.  Work where they
+// cross, millions, measured / this line: 20 depth-6 trees of 127 features
+// 135 / 143, 60 of them 313 / 266, 100 of them 430 / 407, 20 of depth 3 to 8
+// 112 / 103, 30 of 200 features 183 / 169, 30 of 60 features 144 / 127; 60
+// depth-5 trees of 30 features 120 / 100, 30 of them 97 / 88; 100 depth-4 trees
+// of 16 features 92 / 70; lists over 1000 of 3 to 16 features never / below 0
+// (40 depth-6 trees of 8 features, 8192 rows 289 us listed, 160 generated).
+inline int64_t iv_listed_work(int64_t values, int64_t longest) { return 95000000 + 4700 * values - 105000 * longest; }
 constexpr int kWalkPatternBytes = 32768;  // pattern rows of a chunk in LDS
 
 }  // namespace wdf

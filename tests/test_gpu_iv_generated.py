@@ -32,7 +32,7 @@ def _pool():
 
 
 @pytest.mark.parametrize("kind", ["shapley", "banzhaf"])
-@pytest.mark.parametrize("make,n", [(_edge_ensemble, 600_011), (_pool, 33_003)], ids=["edge", "pool"])
+@pytest.mark.parametrize("make,n", [(_edge_ensemble, 1_600_011), (_pool, 33_003)], ids=["edge", "pool"])
 def test_generated_interaction_kernels(wdf, ctx, make, n, kind):
     ens = make()
     F = ens.n_features
@@ -70,8 +70,8 @@ def test_generated_kernels_through_the_scratch_array(wdf, ctx):
     bg = wdf.Background(model, torch.from_numpy(w.background()).cuda(), values=wdf.SHAPLEY_IV)
     F = ens.n_features
     assert bg.iv_workspace_bytes(200_000) <= wdf.NOALLOC_SCRATCH_BYTES
-    X = torch.from_numpy(w.consumers(300_000)).cuda()
-    for a, n in ((0, 200_000), (200_000, 90_001)):
+    X = torch.from_numpy(w.consumers(371_000)).cuda()
+    for a, n in ((0, 200_000), (200_000, 170_001)):
         assert bg.explain_route(n) == wdf.ROUTE_GENERATED
         Xn = X[:, a:a + n].contiguous()
         out = torch.full((F, F, n), float("nan"), device="cuda")
