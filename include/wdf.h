@@ -72,7 +72,7 @@ enum {
 /* Kernel choice for the pattern, histogram and gather steps. */
 enum {
   WDF_KERNEL_AUTO = 0,      /* model-specialised kernels when they compile, else generic */
-  WDF_KERNEL_GENERIC = 1,   /* data-driven kernels that walk each leaf path */
+  WDF_KERNEL_GENERIC = 1,   /* data-driven kernels that walk each tree's tested nodes */
   WDF_KERNEL_SPECIALISED = 2,/* kernels compiled for this ensemble at load time (hipRTC) */
   /* Flag, OR-ed into AUTO or SPECIALISED: the specialised gather reads every
    * sibling pair from its own table (d values at 2^d entries) instead of
@@ -178,10 +178,11 @@ int wdf_pathdep_load(wdf_model *model, int values, void *hip_stream, wdf_bg **ou
 
 void wdf_bg_destroy(wdf_bg *bg);
 
-/* 1 when the summary is explained by model-specialised kernels (Shapley and
- * Banzhaf values: the model's; interaction values: the model's interaction
- * kernels, which very large models do without), 0 for the generic ones or a
- * NULL summary. */
+/* 1 when the summary has model-specialised kernels (Shapley and Banzhaf
+ * values: the model's; interaction values: the model's interaction kernels,
+ * which very large models do without), 0 when it has the generic ones only or
+ * for a NULL summary.  Calls of few rows run data-driven kernels all the same,
+ * with the same values (wdf_debug_explain_route). */
 int wdf_bg_specialised(const wdf_bg *bg);
 
 /* Explain consumer rows against a summary (Section 7 step (g); Alg. 3): each

@@ -134,7 +134,7 @@ constexpr int64_t kBusyColumnTables = 3 << 20;
 // over four streams).  `work` is rows x table values added per row.
 //
 // The gather: its time grows with the work, the F x n / 64 blocks and the
-// entries of the busiest column, which one lane adds in a row.  Measured on 14
+// entries of the busiest column, which one lane adds in a row.  Measured on 18
 // models, us, gather / listed / generated: 20 depth-6 trees of 127 features, 64
 // rows 18 / 36 / 152, 512 rows 46 / 54 / 158, 1024 rows 75 / 61 / 172; 60
 // depth-6 trees of 200 features, 512 rows 130 / 112 / - (a block limit); 40

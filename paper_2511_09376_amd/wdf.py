@@ -413,7 +413,7 @@ class Background:
 
     @property
     def specialised(self) -> bool:
-        """Explained by model-specialised kernels (else the generic ones)."""
+        """Has model-specialised kernels, else the generic ones only (few rows: explain_route)."""
         return bool(lib().wdf_bg_specialised(self.h))
 
     @property
