@@ -920,7 +920,7 @@ extern "C" __global__ __launch_bounds__(NT, 2) void EXPLAIN_NAME(const float* __
   std::vector<Event> ev;
   std::vector<int64_t> event_of(P.xunits.size(), -1);
   std::vector<size_t> batch0;  // first event of every batch
-  const int max_reads = gather_reads((int)std::count(used.begin(), used.end(), (char)1), P.words);
+  const int n_used = (int)std::count(used.begin(), used.end(), (char)1), max_reads = gather_reads(n_used, P.words);
   {
     size_t s = 0;
     int open_reads = 0;
@@ -1058,9 +1058,13 @@ extern "C" __global__ __launch_bounds__(NT, 2) void EXPLAIN_NAME(const float* __
   // stood there together, with the vector units and the LDS idle (paper shape
   // 4.09 ms at once, 3.79 in two halves, 3.74 in quarters).
   // Models of more stages copy at once: the compiler's time grows with the
-  // square of the copies' number (the 500-tree ensemble's 640 stages).
+  // square of the copies' number (the 500-tree ensemble's 640 stages).  So do
+  // models whose accumulators and rank words spill: a wave's waits for its
+  // spilled values then wait for the copies issued since as well (262144 rows,
+  // quarters / at once: 170 features 260 / 263 us, 200 372 / 340, 400 1242 / 1081;
+  // of 1000 features 131072 rows 1217 / 1171, 1182 with the stages confined).
   const int NQ = P.nt_explain / 4;
-  const bool by_quarters = buf_copy && S.size() <= 256;
+  const bool by_quarters = buf_copy && S.size() <= 256 && n_used + P.words <= 220;
   std::vector<std::string> quarters;  // of the stage being copied, not yet issued
   auto start_copy = [&](size_t s) {
     if (s >= S.size()) return;
