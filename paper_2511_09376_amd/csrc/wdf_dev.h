@@ -106,6 +106,10 @@ struct WalkOp {
   uint32_t out;   // bits 0-19 where the slot goes (a pattern row of the chunk, or its first bin), 20-31 mask
 };
 constexpr uint32_t kWalkBias = 1u << 4, kWalkEmit = 1u << 5;
+// levels dropped by a segment's first op: all that P may hold (a path, a quad's
+// two splits and the padding of a segment), so that segments may run on one
+// after another
+constexpr int kWalkDropAll = 15;
 
 // Totally ordered image of a float: x < y iff walk_key(x) < walk_key(y), both
 // zeros alike, every NaN 0 (below all numbers; a bias of 1 wraps it above them).

@@ -473,7 +473,7 @@ extern "C" int wdf_model_load(wdf_ctx *ctx, const wdf_model_desc *desc, int kern
   if (!M->jit) {
     try {
       plan_units(M.get(), INT64_MAX, false);
-      if ((rc = walk_build_explain(M.get())) || (rc = walk_build_hist(M.get()))) return rc;
+      if ((rc = walk_build_explain(M.get(), true)) || (rc = walk_build_hist(M.get()))) return rc;
     } catch (const std::bad_alloc &) {
       return set_error(WDF_E_OOM, "wdf_model_load: out of host memory");
     }

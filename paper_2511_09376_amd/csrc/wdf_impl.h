@@ -140,7 +140,9 @@ constexpr int64_t kBusyColumnTables = 3 << 20;
 // depth-6 trees of 200 features, 512 rows 130 / 112 / - (a block limit); 40
 // depth-6 trees of 8 features, 512 rows 62 / 218 / 141; 200 depth-4 trees over 3
 // features (990 entries in a column), 1024 rows 111 / 179 / 131, 2048 rows
-// 136 / 157 / 119.
+// 136 / 157 / 119; one depth-6 tree of 127, 5000 rows 123 / 82 / 171, 10 depth-4
+// trees of 8, 20000 rows 33 / 24 / 67 (five blocks per CU at most, unless of 512
+// rows: two depth-2 trees of 60, 20000 rows 40 / 42 / 118).
 constexpr int64_t kWalkIvRows = 512, kWalkIvWork = 16 << 20, kWalkIvColumn = 1 << 20;
 // The lists: their time is the longest one's walk plus the work, that of the
 // generated kernels what their launches and table streams take for any number
@@ -153,6 +155,23 @@ constexpr int64_t kWalkIvRows = 512, kWalkIvWork = 16 << 20, kWalkIvColumn = 1 <
 // (40 depth-6 trees of 8 features, 8192 rows 289 us listed, 160 generated).
 inline int64_t iv_listed_work(int64_t values, int64_t longest) { return 95000000 + 4700 * values - 105000 * longest; }
 constexpr int kWalkPatternBytes = 32768;  // pattern rows of a chunk in LDS
+// Small models with many rows: blocks of 512 rows, each wave with all units and
+// columns of its own 64, 64 units' patterns at a time.  In a block of 64 rows most
+// waves of a small model have no segment or column left, and each block of columns
+// stages every feature's keys (or reads them again); a wave by itself needs no
+// barrier, takes its segments as one program and reads the tested features only.
+// Below about 2048 rows per unit of a chunk its longer chain costs more.  1M rows,
+// us, blocks of 64 / of 512 (the kernel before the gather): one depth-3 tree of 4
+// features 91 / 25 (28), two depth-2 trees of 60 201 / 60 (57), 10 depth-3 trees of
+// 127 1059 / 337 (525), 10 depth-4 trees of 8 350 / 226 (514), at 100k rows 45 / 45.
+// With more units only where they are fewer than the features: 400k rows, 40
+// depth-3 trees of 160 (80 units) 1172 / 491 (777), 10 depth-6 trees of 1000 6977 / 2117
+// (3301); 40 depth-4 trees of 127 (160 units) stay at 1185 (1794).
+constexpr int kWalkTallUnits = 64;
+constexpr int64_t kWalkTallFeatures = 1024, kWalkTallRows = 2048;
+inline bool walk_tall(const WalkLevel &L, int64_t n) {
+  return L.max_slots <= kWalkTallUnits && n >= kWalkTallRows * L.max_slots;
+}
 
 }  // namespace wdf
 
@@ -198,6 +217,7 @@ struct wdf_model {
   // data-driven kernels: the explain walk's levels, coarse to fine (rebuilt
   // with the explain-table units), and the generic models' histogram
   std::vector<std::unique_ptr<wdf::WalkLevel>> walk;
+  std::unique_ptr<wdf::WalkLevel> walk_tall;  // small generic models: all columns in blocks of 512 rows (null: none)
   wdf::WalkHist walk_hist;
   std::unique_ptr<wdf::WalkLevel> walk_iv;  // interaction values of few rows (null: none)
 
@@ -297,8 +317,8 @@ Route explain_iv_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx,
 // their folds searched for the generated explain kernel or default (wdf_jit.cpp)
 void plan_units(wdf_model *M, int64_t max_floats, bool generated);
 // Data-driven kernels (wdf_walk.cpp): the plan of the explain walk for the
-// planned units (which it uploads), and of the histogram
-int walk_build_explain(wdf_model *M);
+// planned units (which it uploads; tall: for many rows too), and of the histogram
+int walk_build_explain(wdf_model *M, bool tall);
 int walk_build_hist(wdf_model *M);
 int walk_hist(const wdf_model *M, const float *B, int64_t m, int64_t ldb, uint32_t *hist, hipStream_t s);
 int walk_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, hipStream_t s);

@@ -53,7 +53,8 @@ struct WalkArgs {
   int F, x_off;  // x_off: byte offset of the row keys in LDS (-1: keys read from X)
 };
 // wide: pattern rows of 16-bit slots (else 8-bit); entry_shift: log2 of the
-// bytes between consecutive slots of a table plane
+// bytes between consecutive slots of a table plane; rows per block: 1, 4, 16,
+// 64 or 512
 // LDS sizes of the data-driven kernels on the current device (once per context)
 hipError_t walk_init();
 hipError_t launch_walk(WalkArgs a, int n_groups, int max_slots, bool wide, int entry_shift, int rows, hipStream_t s);

@@ -1360,7 +1360,7 @@ int jit_build(wdf_model *M) {
                                              hipMemcpyHostToDevice, s)) != hipSuccess)
     return hip_error(e, "hipMemcpyAsync(perm)");
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_error(e, "hipStreamSynchronize");
-  if ((rc = walk_build_explain(M))) return rc;
+  if ((rc = walk_build_explain(M, false))) return rc;
   M->jit = mod;
   return WDF_OK;
 }

@@ -132,7 +132,9 @@ __global__ __launch_bounds__(kWalkThreads) void k_hist_walk(const HistWalkArgs a
 // R lanes, one per row: a whole wave for 64 rows (ops and entries are then
 // read through the scalar cache), 64 / R workers per wave for few rows, which
 // would leave most lanes idle and the workers' serial chains 64 / R times as
-// long (one row of the 100-tree depth-6 model: 49 us with 64-row tiles).  The
+// long (one row of the 100-tree depth-6 model: 49 us with 64-row tiles).  With
+// 512 rows (small models, many rows) every wave works by itself, without a
+// barrier: a lane reads the patterns it wrote.  The
 // entries' order is that of the generated explain kernel's adds, so the sums
 // have the same bits.  No scratch outside LDS: calls on any streams may
 // overlap.
@@ -140,9 +142,12 @@ template <typename PT, int ESHIFT, int R>
 __global__ __launch_bounds__(kWalkThreads) void k_walk(const WalkArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t wsmem[];
   constexpr int W = kWalkThreads / R;  // workers
-  constexpr int kBatch = ESHIFT == 4 ? 16 : 4;  // (an interaction column has few entries)
+  // entries of a column in flight (a small model's column and an interaction column have few)
+  constexpr int kBatch = ESHIFT == 4 && R != 512 ? 16 : 4;
   const int r = threadIdx.x & (R - 1);
-  const int worker = R == 64 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64) : (int)threadIdx.x / R;
+  const int worker = R == 512  ? 0
+                     : R == 64 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64)
+                               : (int)threadIdx.x / R;
   PT *pat = (PT *)wsmem + r;
   uint32_t *xt = a.x_off >= 0 ? wsmem + a.x_off / 4 : nullptr;
   const int64_t row0 = (int64_t)blockIdx.x * R, row = row0 + r, rr = row < a.n ? row : a.n - 1;
@@ -152,11 +157,16 @@ __global__ __launch_bounds__(kWalkThreads) void k_walk(const WalkArgs a) {
   if (xt) walk_load_tile<R>(a.X, a.ldx, row0, a.n, a.F, xt);
   for (int c = g.chunk0; c < g.chunk1; ++c) {
     const WalkChunk ch = a.chunks[c];
-    __syncthreads();  // the keys are stored; the last chunk's patterns (and its sums, in memory) are read
-    for (int s = ch.seg0 + worker; s < ch.seg1; s += W)
-      walk_segment<R>(a.ops, a.segs[s], a.X, a.ldx, rr, xt ? xt + r : nullptr,
-                      [&](uint32_t slot, uint32_t o) { pat[o * R] = (PT)slot; });
-    __syncthreads();
+    if (R != 512) __syncthreads();  // the keys are stored; the last chunk's patterns (and its sums, in memory) are read
+    const auto keep = [&](uint32_t slot, uint32_t o) { pat[o * R] = (PT)slot; };
+    if (R == 512) {  // the chunk's segments as one
+      if (ch.seg0 < ch.seg1)
+        walk_segment<R>(a.ops, int2{a.segs[ch.seg0].x, a.segs[ch.seg1 - 1].y}, a.X, a.ldx, rr, nullptr, keep);
+    } else {
+      for (int s = ch.seg0 + worker; s < ch.seg1; s += W)
+        walk_segment<R>(a.ops, a.segs[s], a.X, a.ldx, rr, xt ? xt + r : nullptr, keep);
+    }
+    if (R != 512) __syncthreads();
     const bool first = c == g.chunk0;
     for (int q = ch.run0 + worker; q < ch.run1; q += W) {
       const WalkRun run = a.runs[q];
@@ -474,11 +484,12 @@ __global__ __launch_bounds__(256) void k_pd_freq(const Group *__restrict__ group
 
 namespace {
 using WalkKernel = void (*)(const WalkArgs);
-// [pattern rows and entry stride][rows per block: 1, 4, 16, 64]
-const WalkKernel kWalkKernels[3][4] = {
-    {k_walk<uint8_t, 4, 1>, k_walk<uint8_t, 4, 4>, k_walk<uint8_t, 4, 16>, k_walk<uint8_t, 4, 64>},
-    {k_walk<uint16_t, 4, 1>, k_walk<uint16_t, 4, 4>, k_walk<uint16_t, 4, 16>, k_walk<uint16_t, 4, 64>},
-    {k_walk<uint8_t, 2, 1>, k_walk<uint8_t, 2, 4>, k_walk<uint8_t, 2, 16>, k_walk<uint8_t, 2, 64>}};
+// [pattern rows and entry stride][rows per block: 1, 4, 16, 64, 512]
+const WalkKernel kWalkKernels[3][5] = {
+    {k_walk<uint8_t, 4, 1>, k_walk<uint8_t, 4, 4>, k_walk<uint8_t, 4, 16>, k_walk<uint8_t, 4, 64>, k_walk<uint8_t, 4, 512>},
+    {k_walk<uint16_t, 4, 1>, k_walk<uint16_t, 4, 4>, k_walk<uint16_t, 4, 16>, k_walk<uint16_t, 4, 64>,
+     k_walk<uint16_t, 4, 512>},
+    {k_walk<uint8_t, 2, 1>, k_walk<uint8_t, 2, 4>, k_walk<uint8_t, 2, 16>, k_walk<uint8_t, 2, 64>, k_walk<uint8_t, 2, 512>}};
 }  // namespace
 
 hipError_t walk_init() {
@@ -512,12 +523,12 @@ hipError_t launch_hist_walk(const HistWalkArgs &a, hipStream_t s) {
 
 hipError_t launch_walk(WalkArgs a, int n_groups, int max_slots, bool wide, int entry_shift, int rows, hipStream_t s) {
   if (a.n <= 0 || n_groups <= 0) return hipSuccess;
-  if ((entry_shift != 4 && (entry_shift != 2 || wide)) || (rows != 1 && rows != 4 && rows != 16 && rows != 64))
-    return hipErrorInvalidValue;
+  const int which = rows == 1 ? 0 : rows == 4 ? 1 : rows == 16 ? 2 : rows == 64 ? 3 : rows == 512 ? 4 : -1;
   size_t lds = ((size_t)max_slots * rows * (wide ? 2 : 1) + 15) / 16 * 16;
-  a.x_off = a.F <= kWalkXFeatures ? (int)lds : -1;
+  if ((entry_shift != 4 && (entry_shift != 2 || wide)) || which < 0 || lds > 64 * 1024) return hipErrorInvalidValue;
+  a.x_off = a.F <= kWalkXFeatures && rows <= 64 ? (int)lds : -1;
   if (a.x_off >= 0) lds += (size_t)a.F * rows * 4;
-  const WalkKernel f = kWalkKernels[entry_shift == 2 ? 2 : wide ? 1 : 0][rows == 1 ? 0 : rows == 4 ? 1 : rows == 16 ? 2 : 3];
+  const WalkKernel f = kWalkKernels[entry_shift == 2 ? 2 : wide ? 1 : 0][which];
   // a launch holds fewer than 2^32 threads per grid dimension: more rows go in several
   const int64_t n = a.n, most = (int64_t)(0xffffffffu / kWalkThreads) * rows;
   for (int64_t r0 = 0; r0 < n; r0 += most) {

@@ -57,7 +57,7 @@ class Programs {
         int at = 0;
         while (at < have && at < u.levels && on[at] == path[at]) ++at;
         for (; at < u.levels; ++at) {
-          test(path[at], have - at);
+          test(path[at], ops.size() == op0 ? kWalkDropAll : have - at);
           on[at] = path[at];
           have = at + 1;
         }
@@ -154,11 +154,13 @@ int guarded(Build build) {
   }
 }
 
+// units whose patterns a block of 64 rows holds
+int chunk_units(bool wide) { return kWalkPatternBytes / 64 / (wide ? 2 : 1); }
+
 constexpr int kZeroRun = 32;  // columns one wave clears at a time
 
 int build_level(const wdf_model *M, const std::vector<WalkUnit> &units, const std::vector<ColumnGroup> &groups,
-                bool wide, int entry_shift, WalkLevel &out) {
-  const int cap = kWalkPatternBytes / 64 / (wide ? 2 : 1);
+                bool wide, int entry_shift, int cap, WalkLevel &out) {
   Programs prog(M);
   std::vector<WalkGroup> gs;
   std::vector<WalkChunk> chunks;
@@ -242,13 +244,12 @@ int build_level(const wdf_model *M, const std::vector<WalkUnit> &units, const st
 
 }  // namespace
 
-// Levels of the explain walk, coarse to fine: columns (features) per block.  A
-// coarse level computes a unit's slot for few blocks of columns, a fine one
-// spreads few rows over more blocks; each is used for the row counts where its
-// blocks just fill the device (launch).
-static const int kWalkColumns[] = {64, 16, 4};
-
-static int build_explain(wdf_model *M) {
+// Levels of the explain walk, coarse to fine: columns (features) per block, 64,
+// 16 and 4.  A coarse level computes a unit's slot for few blocks of columns, a
+// fine one spreads few rows over more blocks; each is used for the row counts
+// where its blocks just fill the device (walk_explain).  Small generic models
+// have one more, of all columns, for blocks of 512 rows.
+static int build_explain(wdf_model *M, bool tall) {
   JitPlan &P = M->jp;
   const int F = M->n_features;
   int rc;
@@ -281,11 +282,7 @@ static int build_explain(wdf_model *M) {
       if (pn.first) cols[(size_t)pn.feat].push_back(ColumnEntry{(int32_t)u, x.dst + (v / 4) * 4 * E + v % 4});
     }
   }
-  M->walk.clear();
-  for (int per : kWalkColumns) {
-    // finer levels repeat the programs in more groups: one level for the
-    // largest models, and none finer than the first that splits nothing
-    if (!M->walk.empty() && ((int64_t)P.xunits.size() > 100000 || F <= per)) continue;
+  auto column_groups = [&](int per) {
     std::vector<ColumnGroup> groups;
     for (int c0 = 0; c0 < F; c0 += per) {
       ColumnGroup g{c0, std::min(per, F - c0), {}};
@@ -293,9 +290,21 @@ static int build_explain(wdf_model *M) {
         if (!cols[(size_t)c].empty()) g.lists.push_back({c - c0, &cols[(size_t)c]});
       groups.push_back(std::move(g));
     }
+    return groups;
+  };
+  M->walk.clear();
+  for (int per : {64, 16, 4}) {
+    // finer levels repeat the programs in more groups: one level for the
+    // largest models, and none finer than the first that splits nothing
+    if (!M->walk.empty() && ((int64_t)P.xunits.size() > 100000 || F <= per)) continue;
     M->walk.emplace_back(new WalkLevel());
-    rc = build_level(M, units, groups, wide, 4, *M->walk.back());
+    rc = build_level(M, units, column_groups(per), wide, 4, chunk_units(wide), *M->walk.back());
     if (rc) return rc;
+  }
+  M->walk_tall.reset();
+  if (tall && (int64_t)units.size() <= std::max<int64_t>(kWalkTallUnits, std::min<int64_t>(F, kWalkTallFeatures))) {
+    M->walk_tall.reset(new WalkLevel());
+    if ((rc = build_level(M, units, column_groups(F), wide, 4, kWalkTallUnits, *M->walk_tall))) return rc;
   }
   return WDF_OK;
 }
@@ -330,7 +339,7 @@ static int build_iv(wdf_model *M) {
     groups.push_back(std::move(g));
   }
   std::unique_ptr<WalkLevel> L(new WalkLevel());
-  const int rc = build_level(M, units, groups, false, 2, *L);
+  const int rc = build_level(M, units, groups, false, 2, chunk_units(false), *L);
   if (rc == WDF_E_UNSUPPORTED) return WDF_OK;
   if (rc) return rc;
   M->walk_iv = std::move(L);
@@ -383,8 +392,8 @@ static int build_hist(wdf_model *M) {
   return up.run(W.buf, M->ctx->stream);
 }
 
-int walk_build_explain(wdf_model *M) {
-  return guarded([&] { return build_explain(M); });
+int walk_build_explain(wdf_model *M, bool tall) {
+  return guarded([&] { return build_explain(M, tall); });
 }
 int walk_build_hist(wdf_model *M) {
   return guarded([&] { return build_hist(M); });
@@ -405,12 +414,13 @@ int walk_hist(const wdf_model *M, const float *B, int64_t m, int64_t ldb, uint32
 }
 
 // level L's columns for n rows: the fewest rows per block that stay within two
-// blocks per CU, else 64
+// blocks per CU, else 64, or 512 (walk_tall)
 static int walk_launch(const wdf_model *M, const WalkLevel &L, const float *tab, const float *X, int64_t n, int64_t ldx,
                        float *out, int64_t ldo, hipStream_t s) {
   const int64_t blocks = 2 * (int64_t)M->ctx->n_cu;
   int rows = 1;
   while (rows < 64 && (n + rows - 1) / rows * L.n_groups > blocks) rows *= 4;
+  if (walk_tall(L, n)) rows = 512;
   const WalkArgs a{X, ldx, n, out, ldo, tab, L.ops, L.segs, L.groups, L.chunks, L.runs, L.entries, M->n_features, 0};
   HIP_TRY(launch_walk(a, L.n_groups, L.max_slots, L.wide, L.entry_shift, rows, s));
   return WDF_OK;
@@ -420,6 +430,8 @@ int walk_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float
   const wdf_model *M = bg->model;
   // the coarsest level whose 64-row blocks fill the device (two per CU), for
   // fewer rows the finest
+  if (M->walk_tall && n >= kWalkTallRows * M->walk_tall->max_slots)
+    return walk_launch(M, *M->walk_tall, bg->d_xtab.as<float>(), X, n, ldx, phi, ldphi, s);
   const int64_t blocks = 2 * (int64_t)M->ctx->n_cu, tiles = (n + 63) / 64;
   const WalkLevel *L = nullptr;
   for (const auto &l : M->walk) {

@@ -86,3 +86,45 @@ def test_few_features_keep_the_generated_kernel(wdf, ctx, spec):
     for n in (1, 64, 600):
         assert a.explain_route(n) == wdf.ROUTE_GENERATED and b.explain_route(n) == wdf.ROUTE_GATHER
         torch.testing.assert_close(a.explain(X[:, :n]), b.explain(X[:, :n]), rtol=0, atol=1e-5 * float(b.explain(X).abs().max()))
+
+
+# trees, depths, features: stumps; unused features; 80 units in chunks of 64; a unit
+# of 512 entries (16-bit slots); a chunk of exactly 64
+@pytest.mark.parametrize("spec", [(3, 1, 1, 4), (2, 2, 2, 60), (40, 3, 3, 160), (1, 8, 8, 30), (30, 1, 8, 300), (16, 4, 4, 20)])
+def test_small_generic_models_with_many_rows(wdf, ctx, spec):
+    """Blocks of 512 rows (at least 2048 rows per unit of a chunk) against blocks
+    of few rows, bit for bit, and the oracle; nothing outside the output."""
+    trees, lo, hi, F = spec
+    ens = synth.make_ensemble(synth.ModelSpec(trees, lo, hi, 0.1 if lo != hi else 0.0, F), synth.DataSpec(F, False, 0.05), 5)
+    n = 2048 * 64 + 333
+    head = _rows(ens, 4000)
+    X = torch.from_numpy(head).cuda().repeat(1, n // 4000 + 1)[:, :n + 1]
+    model = wdf.Model(ctx, ens, wdf.KERNEL_GENERIC)
+    bg = wdf.Background(model, X[:, :500].contiguous())
+    few = bg.explain(X[:, :1024])
+    out = torch.full((F, n + 70), 7.0, device="cuda")
+    bg.explain(X[:, :n], out=out[:, 33:33 + n])                      # a slice: strides, ragged last block
+    assert bool((out[:, :33] == 7).all()) and bool((out[:, 33 + n:] == 7).all())
+    phi = out[:, 33:33 + n]
+    assert torch.equal(phi[:, :1024], few)
+    for a in (1024, 4000 * 7 + 5, n - 1024):
+        assert torch.equal(phi[:, a:a + 1024], bg.explain(X[:, a:a + 1024])), a
+    ref = oracle.bg_walk(oracle.Model(ens), np.ascontiguousarray(head[:, :24]), np.ascontiguousarray(head[:, :500]), threads=8)
+    assert_phi_close(phi[:, :24].cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("spec", [(3, 2, 4), (2, 2, 60)])
+def test_small_interaction_models_with_many_rows(wdf, ctx, spec):
+    trees, depth, F = spec
+    ens = synth.make_ensemble(synth.ModelSpec(trees, depth, depth, 0.0, F), synth.DataSpec(F, False, 0.05), 5)
+    n = 40_001
+    X = torch.from_numpy(_rows(ens, n)).cuda()
+    bg = wdf.Background(wdf.Model(ctx, ens, wdf.KERNEL_GENERIC), X[:, :500].contiguous(), values=wdf.BANZHAF_IV)
+    assert bg.explain_route(n) == wdf.ROUTE_GATHER
+    iv = bg.explain_iv(X)
+    for a in (0, 20_003, n - 700):
+        assert torch.equal(iv[:, :, a:a + 700], bg.explain_iv(X[:, a:a + 700])), a
+    ref = oracle.bg_iv_walk(oracle.Model(ens), np.ascontiguousarray(X[:, :16].cpu().numpy()),
+                            np.ascontiguousarray(X[:, :500].cpu().numpy()), oracle.BANZHAF, threads=8)
+    g = iv[:, :, :16].cpu().numpy().reshape(F * F, -1)
+    assert (np.abs(g - ref.reshape(F * F, -1)).max(0) / np.maximum(np.abs(ref).reshape(F * F, -1).max(0), 1e-30)).max() <= 1e-5
