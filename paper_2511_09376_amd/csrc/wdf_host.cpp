@@ -1004,7 +1004,8 @@ Route wdf::explain_iv_route(const wdf_bg *bg, const float *X, int64_t n, int64_t
   const int64_t work = n * M->iv_values, F = M->n_features, tiles = F * ((n + 63) / 64), n_cu = M->ctx->n_cu;
   const WalkLevel *L = M->walk_iv.get();
   const bool few = L && ((n <= kWalkIvRows && 2 * tiles <= 7 * n_cu) ||
-                         (work <= kWalkIvWork && n * L->max_column <= kWalkIvColumn));
+                         (work <= kWalkIvWork && n * L->max_column <= kWalkIvColumn &&
+                          (tiles <= 5 * n_cu || walk_tall(*L, n))));
   if (few && !may_share(X, ldx, F, iv, ldiv, F * F, n)) return Route::gather;
   return bg->iv_spec && work > iv_listed_work(M->iv_values, M->iv_longest) ? Route::generated : Route::listed;
 }
