@@ -112,6 +112,8 @@ def _model(trees, depth, F, pool=0):
     ((200, 4, 8, 3), {512: 1, 1024: 1, 2048: 0, 9000: 0}),       # 990 entries in a column, lists of 2000
     ((40, 6, 8), {512: 1, 800: 1, 1024: 0}),                     # lists of 2700
     ((20, 6, 127), {1: 1, 600: 1, 1024: 2, 7000: 2, 8192: 0}),
+    ((1, 6, 127), {200: 1, 5000: 2}),                            # little work, many blocks
+    ((10, 4, 8), {5000: 1, 20000: 2}),
 ], ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else "")
 def test_interaction_routes(wdf, ctx, spec, routes):
     ens, data = _model(*spec)
