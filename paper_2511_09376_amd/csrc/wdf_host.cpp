@@ -1013,7 +1013,8 @@ Route wdf::explain_iv_route(const wdf_bg *bg, const float *X, int64_t n, int64_t
 extern "C" int wdf_debug_explain_route(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, const float *out,
                                        int64_t ldo) {
   if (!bg) return set_error(WDF_E_INVALID_ARG, "wdf_debug_explain_route: NULL summary");
-  if (n < 1 || ldx < n || ldo < n) return set_error(WDF_E_INVALID_ARG, "wdf_debug_explain_route: need 1 <= n <= ldx, ldo");
+  if (n < 1 || ldx < n || ldo < n)
+    return set_error(WDF_E_INVALID_ARG, "wdf_debug_explain_route: need 1 <= n <= ldx, ldo");
   return (int)(bg->iv ? explain_iv_route(bg, X, n, ldx, out, ldo) : explain_route(bg, X, n, ldx, out, ldo));
 }
 

@@ -486,10 +486,12 @@ namespace {
 using WalkKernel = void (*)(const WalkArgs);
 // [pattern rows and entry stride][rows per block: 1, 4, 16, 64, 512]
 const WalkKernel kWalkKernels[3][5] = {
-    {k_walk<uint8_t, 4, 1>, k_walk<uint8_t, 4, 4>, k_walk<uint8_t, 4, 16>, k_walk<uint8_t, 4, 64>, k_walk<uint8_t, 4, 512>},
+    {k_walk<uint8_t, 4, 1>, k_walk<uint8_t, 4, 4>, k_walk<uint8_t, 4, 16>, k_walk<uint8_t, 4, 64>,
+     k_walk<uint8_t, 4, 512>},
     {k_walk<uint16_t, 4, 1>, k_walk<uint16_t, 4, 4>, k_walk<uint16_t, 4, 16>, k_walk<uint16_t, 4, 64>,
      k_walk<uint16_t, 4, 512>},
-    {k_walk<uint8_t, 2, 1>, k_walk<uint8_t, 2, 4>, k_walk<uint8_t, 2, 16>, k_walk<uint8_t, 2, 64>, k_walk<uint8_t, 2, 512>}};
+    {k_walk<uint8_t, 2, 1>, k_walk<uint8_t, 2, 4>, k_walk<uint8_t, 2, 16>, k_walk<uint8_t, 2, 64>,
+     k_walk<uint8_t, 2, 512>}};
 }  // namespace
 
 hipError_t walk_init() {

@@ -81,7 +81,8 @@ class Programs {
     const uint32_t bias = M_->default_left[(size_t)node] ? 0u : 1u;
     uint32_t b;
     std::memcpy(&b, &M_->threshold[(size_t)node], sizeof b);
-    ops.push_back(WalkOp{M_->feature[(size_t)node], walk_key_bits(b) - bias, (uint32_t)drop | (bias ? kWalkBias : 0u), 0u});
+    ops.push_back(WalkOp{M_->feature[(size_t)node], walk_key_bits(b) - bias,
+                         (uint32_t)drop | (bias ? kWalkBias : 0u), 0u});
   }
 
   const wdf_model *M_;
@@ -428,10 +429,10 @@ static int walk_launch(const wdf_model *M, const WalkLevel &L, const float *tab,
 
 int walk_explain(const wdf_bg *bg, const float *X, int64_t n, int64_t ldx, float *phi, int64_t ldphi, hipStream_t s) {
   const wdf_model *M = bg->model;
+  if (M->walk_tall && walk_tall(*M->walk_tall, n))
+    return walk_launch(M, *M->walk_tall, bg->d_xtab.as<float>(), X, n, ldx, phi, ldphi, s);
   // the coarsest level whose 64-row blocks fill the device (two per CU), for
   // fewer rows the finest
-  if (M->walk_tall && n >= kWalkTallRows * M->walk_tall->max_slots)
-    return walk_launch(M, *M->walk_tall, bg->d_xtab.as<float>(), X, n, ldx, phi, ldphi, s);
   const int64_t blocks = 2 * (int64_t)M->ctx->n_cu, tiles = (n + 63) / 64;
   const WalkLevel *L = nullptr;
   for (const auto &l : M->walk) {
